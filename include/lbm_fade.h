@@ -61,10 +61,12 @@ enum { LBM_D2Q5 = 5, LBM_D3Q7 = 7 };
 enum { LBM_BGK = 0, LBM_MRT = 1 };
 
 /* Arithmetic of the fractional-term GEMM.  Weights are always generated in FP64.
- *   LBM_FP32   FP32 operands on FP32 MFMA, FP32 accumulation;
+ *   LBM_FP32   FP32 operands and FP32 accumulation, on FP32 MFMA or (long
+ *              axes) as exact three-term BF16 splits on BF16 MFMA;
  *   LBM_BF16X3 3-term split BF16: W = W_hi + W_lo, C = C_hi + C_lo (round to
  *              nearest even), W_hi C_hi + W_hi C_lo + W_lo C_hi on BF16 MFMA with
- *              FP32 accumulation (the lo*lo term is dropped);
+ *              FP32 accumulation (the lo*lo term is dropped; the far part of
+ *              long axes is formed as for LBM_FP32);
  *   LBM_FP32_SIMT  FP32 fused multiply-add on the vector units (no MFMA); a
  *              plain kernel kept as a second implementation of the operator. */
 enum { LBM_FP32 = 0, LBM_BF16X3 = 1, LBM_FP32_SIMT = 2 };
@@ -185,10 +187,10 @@ LBM_API int lbm_fade_apply_phi(lbm_fade_t h, const float* C, float* Phi, int32_t
  * floats, Phi[mu*nodes + node]) are device pointers on the current device,
  * ordered on `stream`; they are only borrowed.  The operator data (the
  * Toeplitz generator, boundary columns and BF16 splits of every axis) are
- * placed in a fixed device array of LBM_NOALLOC_SCRATCH_BYTES bytes that the
- * library holds on every device it runs on until the process ends: the call
- * needs about 40 n bytes per axis of n nodes and returns LBM_EINVAL, naming
- * the size, for a grid beyond that.  Every call on a device uses that
+ * placed in a fixed device array that the library holds on every device it
+ * runs on until the process ends: the call needs about 40 n bytes per axis of
+ * n nodes of LBM_NOALLOC_SCRATCH_BYTES and returns LBM_EINVAL, naming the
+ * size, for a grid beyond that.  Every call on a device uses that
  * device's one array, so calls that overlap on one device (other host
  * threads, or other streams before this call's kernels have finished) race;
  * calls ordered on one stream are safe.  Synchronises `stream` once (after

@@ -522,7 +522,7 @@ bool build_ops(lbm_fade* h, AdjointState* A)
         // column, the end columns included)
         {
             const double gm = 2.0 - h->params.alpha[mu];
-            const double empty = pow(0.0, gm);  // c+_{00} = c-_{NN}
+            const double empty = C.pg[0];  // c+_{00} = c-_{NN} = 0^gamma
             std::vector<double> d0(n, 0.0), dN(n, 0.0);
             for (int j = 1; j <= N; ++j) d0[j] = s * (C.cp0[j] - C.a[j]);
             for (int j = 0; j <= N - 1; ++j) dN[j] = -s * (C.cmN[j] - C.a[N - j]);
@@ -530,8 +530,8 @@ bool build_ops(lbm_fade* h, AdjointState* A)
             dN[N] = -s * (empty - 1.0);
             if (h->params.flux_form == 1) {
                 for (int j = 0; j <= N; ++j) {
-                    d0[j] -= s * (1.0 + gm) * pow((double)j, gm);
-                    dN[j] += s * (1.0 + gm) * pow((double)(N - j), gm);
+                    d0[j] -= s * (1.0 + gm) * C.pg[j];
+                    dN[j] += s * (1.0 + gm) * C.pg[N - j];
                 }
             }
             for (int j = 0; j <= N; ++j) {
@@ -548,7 +548,8 @@ bool build_ops(lbm_fade* h, AdjointState* A)
         U.gen = reinterpret_cast<const float*>(base + oU);
         U.col0 = U.colN = zeros;
         U.gen_hi = U.gen_lo = nullptr;
-        U.pw_hi = U.pw_lo = nullptr;
+        U.pw_hi = U.pw_lo = U.pw_l3 = nullptr;
+        U.far_m = U.far_uv = nullptr;
         AxisOp& L = A->opsL[mu];
         L = U;
         L.lower_only = 1;

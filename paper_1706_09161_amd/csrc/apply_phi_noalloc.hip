@@ -21,16 +21,29 @@
 
 namespace {
 
+// The limit on the grid: about 40 n bytes per axis (generator, boundary
+// columns, two BF16 planes) within LBM_NOALLOC_SCRATCH_BYTES.  The third BF16
+// plane (4 n) and the far-box operators (axes of at most 4096 nodes: below
+// 150 KB each) lie in kMoreBytes on top.
 constexpr size_t kScratchBytes = size_t(16) << 20;  // LBM_NOALLOC_SCRATCH_BYTES
+constexpr size_t kMoreBytes = size_t(4) << 20;
 static_assert(kScratchBytes == LBM_NOALLOC_SCRATCH_BYTES, "header and library agree on the scratch size");
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kMoreBytes];
 
 std::mutex g_scratch_mutex;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
 
 int fail(int code, const std::string& msg) { return lbm::set_error(code, msg.c_str()); }
+
+// Bytes of an axis that count towards the limit.
+size_t axis_need(size_t n)
+{
+    auto r256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    return r256(4 * (2 * n - 1)) + 2 * r256(4 * n) + 2 * r256(2 * (2 * n - 1)) +
+           2 * r256(4 * ((size_t)lbm::pw_top_of((int)n) + n + 32));
+}
 
 // Device address of this device's copy of `scratch` (looked up on the first
 // call with the device current, then kept).
@@ -58,9 +71,11 @@ extern "C" int lbm_fade_apply_phi_noalloc(const lbm_grid* grid, const lbm_params
     int rc = lbm::validate_config(grid, 2 * grid->dim + 1, params);
     if (rc) return rc;
     const int64_t nodes = (int64_t)grid->n[0] * grid->n[1] * (grid->dim == 3 ? grid->n[2] : 1);
-    const size_t op_bytes = lbm::operator_image_bytes(*grid);
-    const size_t need = op_bytes;
-    if (need > kScratchBytes)
+    size_t upload = 0;
+    const size_t op_bytes = lbm::operator_image_bytes(*grid, &upload);
+    size_t need = 0;
+    for (int mu = 0; mu < grid->dim; ++mu) need += axis_need((size_t)grid->n[mu]);
+    if (need > kScratchBytes || op_bytes > kScratchBytes + kMoreBytes)
         return fail(LBM_EINVAL, "grid too large for the no-allocation entry point: needs " + std::to_string(need) +
                                     " bytes of its " + std::to_string(kScratchBytes) + "-byte device scratch");
     int dev = 0;
@@ -77,14 +92,16 @@ extern "C" int lbm_fade_apply_phi_noalloc(const lbm_grid* grid, const lbm_params
 
     lbm::AxisOp ops[3];
     lbm::AxisLayout lays[3];
-    std::vector<unsigned char> host(op_bytes, 0);
+    std::vector<unsigned char> host(upload, 0);
     lbm::build_operator_image(*grid, *params, host.data(), base, ops);
     lbm::make_layouts(*grid, lays);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // the host image is pageable memory freed on return: wait for the copy
-    e = hipMemcpyAsync(base, host.data(), op_bytes, hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(base, host.data(), upload, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("upload of operator data: ") + hipGetErrorString(e));
+    e = lbm::launch_far_tables(ops, grid->dim, s);
+    if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("far-box operators: ") + hipGetErrorString(e));
     e = lbm::launch_fractional(ops, lays, grid->dim, params->precision, C, 0, Phi, nodes, s);
     if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("fractional term: ") + hipGetErrorString(e));
     return LBM_OK;

@@ -147,18 +147,18 @@ AxisCoeffs axis_coeffs(int n, double gamma, double g, double dx)
     const double gp1 = gamma + 1.0;
     AxisCoeffs A;
     A.s = g * pow(dx, gamma) / tgamma(2.0 + gamma);
+    // k^gamma and k^{gamma+1}, each power taken once
+    std::vector<double> q(n + 1);
+    A.pg.assign(n, 0.0);
+    for (int k = 0; k <= n; ++k) q[k] = pow((double)k, gp1);
+    for (int k = 0; k <= N; ++k) A.pg[k] = pow((double)k, gamma);
     A.a.assign(n, 0.0);
     A.cp0.assign(n, 0.0);
     A.cmN.assign(n, 0.0);
     A.a[0] = 1.0;
-    for (int k = 1; k <= N; ++k)
-        A.a[k] = pow((double)(k + 1), gp1) - 2.0 * pow((double)k, gp1) + pow((double)(k - 1), gp1);
-    for (int j = 1; j <= N; ++j)
-        A.cp0[j] = (1.0 + gamma) * pow((double)j, gamma) - pow((double)j, gp1) + pow((double)(j - 1), gp1);
-    for (int j = 0; j <= N - 1; ++j) {
-        const int m = N - j;
-        A.cmN[j] = (1.0 + gamma) * pow((double)m, gamma) - pow((double)m, gp1) + pow((double)(m - 1), gp1);
-    }
+    for (int k = 1; k <= N; ++k) A.a[k] = q[k + 1] - 2.0 * q[k] + q[k - 1];
+    for (int j = 1; j <= N; ++j) A.cp0[j] = (1.0 + gamma) * A.pg[j] - q[j] + q[j - 1];
+    for (int j = 0; j <= N - 1; ++j) A.cmN[j] = A.cp0[N - j];  // the same function of the distance to the end
     return A;
 }
 }  // namespace lbm
@@ -185,6 +185,7 @@ struct AxisWeights {
     std::vector<double> T;     // T(d) at d + N, d in [-N, N]
     std::vector<double> col0;  // n: K[j][0]
     std::vector<double> colN;  // n: K[j][N]
+    double s;                  // g dx^gamma / Gamma(2 + gamma)
 };
 
 AxisWeights make_axis_weights(int n, double gamma, double p, double g, double dx, int flux_form)
@@ -193,6 +194,7 @@ AxisWeights make_axis_weights(int n, double gamma, double p, double g, double dx
     const lbm::AxisCoeffs A = lbm::axis_coeffs(n, gamma, g, dx);
     const double s = A.s;
     AxisWeights W;
+    W.s = s;
     W.T.assign(2 * N + 1, 0.0);
     W.col0.assign(n, 0.0);
     W.colN.assign(n, 0.0);
@@ -203,15 +205,15 @@ AxisWeights make_axis_weights(int n, double gamma, double p, double g, double dx
         else v = s * (p * 1.0 + (1.0 - p) * 1.0);
         W.T[d + N] = v;
     }
-    const double empty = pow(0.0, gamma);  // c+_{00} = c-_{NN}
+    const double empty = A.pg[0];  // c+_{00} = c-_{NN} = 0^gamma
     for (int j = 1; j <= N; ++j) W.col0[j] = s * p * A.cp0[j];
     for (int j = 0; j <= N - 1; ++j) W.colN[j] = s * (1.0 - p) * A.cmN[j];
     W.col0[0] = s * (p * empty + (1.0 - p));
     W.colN[N] = s * (p + (1.0 - p) * empty);
     if (flux_form == 1) {
         for (int j = 0; j <= N; ++j) {
-            W.col0[j] -= s * p * (1.0 + gamma) * pow((double)j, gamma);
-            W.colN[j] -= s * (1.0 - p) * (1.0 + gamma) * pow((double)(N - j), gamma);
+            W.col0[j] -= s * p * (1.0 + gamma) * A.pg[j];
+            W.colN[j] -= s * (1.0 - p) * (1.0 + gamma) * A.pg[N - j];
         }
     }
     return W;
@@ -527,18 +529,52 @@ int validate_config(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     return validate(grid, lattice, params);
 }
 
+// The interpolation fragments (the same for every axis), built once.
+static const std::vector<uint16_t>& far_uv_table()
+{
+    static const std::vector<uint16_t> t = [] {
+        std::vector<uint16_t> v(kFarUvEntries);
+        far_uv_fill(v.data(), bf16_from_double, bf16_to_float);
+        return v;
+    }();
+    return t;
+}
+
 // Every piece of the operator data sits at a 256-byte aligned offset.
 static size_t r256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-size_t operator_image_bytes(const lbm_grid& grid)
+// Image: per axis the generator, boundary columns, BF16 splits and pair words,
+// then the interpolation fragments (once), then every long axis' far-box
+// operators (filled on the device).  Only the first `upload` bytes are copied.
+size_t operator_image_bytes(const lbm_grid& grid, size_t* upload)
 {
-    size_t bytes = 0;
+    size_t bytes = 0, tables = 0;
+    bool far = false;
     for (int mu = 0; mu < grid.dim; ++mu) {
         const size_t n = (size_t)grid.n[mu];
         bytes += r256(sizeof(float) * (2 * n - 1)) + 2 * r256(sizeof(float) * n) +
                  2 * r256(sizeof(uint16_t) * (2 * n - 1)) + 2 * r256(sizeof(uint32_t) * pw_len_of((int)n));
+        if (far_used((int)n)) {
+            far = true;
+            bytes += r256(sizeof(uint32_t) * pw_len_of((int)n));
+            tables += r256(sizeof(uint16_t) * far_table_entries((int)n));
+        }
     }
-    return bytes;
+    if (far) bytes += r256(sizeof(uint16_t) * kFarUvEntries);
+    *upload = bytes;
+    return bytes + tables;
+}
+
+// Pair words of one BF16 plane (gen[d + n - 1], d = -(n - 1) ... n - 1), d
+// decreasing from pw_top; the words outside the generator stay as they are (0).
+static void fill_pair_words(const uint16_t* gen, int n, uint32_t* pw)
+{
+    const int top = pw_top_of(n);
+    for (int d = n; d >= -(n - 1); --d) {
+        const uint32_t lo = d <= n - 1 ? gen[d + n - 1] : 0u;
+        const uint32_t hi = d - 1 >= -(n - 1) ? gen[d - 1 + n - 1] : 0u;
+        pw[top - d] = lo | (hi << 16);
+    }
 }
 
 void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned char* host, const unsigned char* base,
@@ -550,6 +586,7 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         off += r256(nbytes);
         return o;
     };
+    bool far = false;
     for (int mu = 0; mu < grid.dim; ++mu) {
         const int n = grid.n[mu];
         const AxisWeights W = make_axis_weights(n, 2.0 - P.alpha[mu], P.p[mu], P.g[mu], grid.dx, P.flux_form);
@@ -558,24 +595,28 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         op.lower_only = P.p[mu] == 1.0;
         op.upper_only = P.p[mu] == 0.0;
         op.ends_excluded = 1;
+        const bool third = far_used(n);
+        far = far || third;
         const size_t og = carve(sizeof(float) * (2 * n - 1));
         const size_t o0 = carve(sizeof(float) * n);
         const size_t oN = carve(sizeof(float) * n);
         const size_t oh = carve(sizeof(uint16_t) * (2 * n - 1));
         const size_t ol = carve(sizeof(uint16_t) * (2 * n - 1));
-        const int64_t pwn = pw_len_of(n);
-        const size_t oph = carve(sizeof(uint32_t) * pwn);
-        const size_t opl = carve(sizeof(uint32_t) * pwn);
+        const size_t pwb = sizeof(uint32_t) * pw_len_of(n);
+        const size_t oph = carve(pwb), opl = carve(pwb), op3 = third ? carve(pwb) : 0;
         float* g = reinterpret_cast<float*>(host + og);
         float* c0 = reinterpret_cast<float*>(host + o0);
         float* cN = reinterpret_cast<float*>(host + oN);
         uint16_t* gh = reinterpret_cast<uint16_t*>(host + oh);
         uint16_t* glo = reinterpret_cast<uint16_t*>(host + ol);
+        std::vector<uint16_t> gl3(third ? 2 * n - 1 : 0);
         for (int t = 0; t < 2 * n - 1; ++t) {
             const double v = W.T[t];
             g[t] = (float)v;
             gh[t] = bf16_from_double(v);
-            glo[t] = bf16_from_double(v - (double)bf16_to_float(gh[t]));
+            const double r = v - (double)bf16_to_float(gh[t]);
+            glo[t] = bf16_from_double(r);
+            if (third) gl3[t] = bf16_from_double(r - (double)bf16_to_float(glo[t]));
         }
         // the whole boundary columns K[j][0] and K[j][N]: the kernels leave
         // k = 0 and k = N out of the Toeplitz sum, so no product of T with a
@@ -585,17 +626,9 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
             cN[j] = (float)W.colN[j];
         }
         // pair words of the BF16 split, d decreasing (operand order of the BF16 GEMM)
-        uint32_t* pwh = reinterpret_cast<uint32_t*>(host + oph);
-        uint32_t* pwl = reinterpret_cast<uint32_t*>(host + opl);
-        const int top = pw_top_of(n);
-        auto bits = [&](const uint16_t* b, int64_t dd) -> uint32_t {
-            return (dd >= -(n - 1) && dd <= n - 1) ? (uint32_t)b[dd + n - 1] : 0u;
-        };
-        for (int64_t x = 0; x < pwn; ++x) {
-            const int64_t dd = top - x;
-            pwh[x] = bits(gh, dd) | (bits(gh, dd - 1) << 16);
-            pwl[x] = bits(glo, dd) | (bits(glo, dd - 1) << 16);
-        }
+        fill_pair_words(gh, n, reinterpret_cast<uint32_t*>(host + oph));
+        fill_pair_words(glo, n, reinterpret_cast<uint32_t*>(host + opl));
+        if (third) fill_pair_words(gl3.data(), n, reinterpret_cast<uint32_t*>(host + op3));
         op.gen = reinterpret_cast<const float*>(base + og);
         op.col0 = reinterpret_cast<const float*>(base + o0);
         op.colN = reinterpret_cast<const float*>(base + oN);
@@ -603,7 +636,21 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         op.gen_lo = reinterpret_cast<const uint16_t*>(base + ol);
         op.pw_hi = reinterpret_cast<const uint32_t*>(base + oph);
         op.pw_lo = reinterpret_cast<const uint32_t*>(base + opl);
-        op.pw_top = top;
+        op.pw_l3 = third ? reinterpret_cast<const uint32_t*>(base + op3) : nullptr;
+        op.pw_top = pw_top_of(n);
+        op.far_m = op.far_uv = nullptr;
+        op.far_g = 2.0 - P.alpha[mu];
+        op.far_pos = W.s * P.p[mu];
+        op.far_neg = W.s * (1.0 - P.p[mu]);
+    }
+    if (!far) return;
+    const size_t ou = carve(sizeof(uint16_t) * kFarUvEntries);
+    const std::vector<uint16_t>& uv = far_uv_table();
+    memcpy(host + ou, uv.data(), sizeof(uint16_t) * uv.size());
+    for (int mu = 0; mu < grid.dim; ++mu) {
+        if (!far_used(grid.n[mu])) continue;
+        ops[mu].far_m = reinterpret_cast<const uint16_t*>(base + carve(sizeof(uint16_t) * far_table_entries(grid.n[mu])));
+        ops[mu].far_uv = reinterpret_cast<const uint16_t*>(base + ou);
     }
 }
 
@@ -686,19 +733,28 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     cc.c_wall = (float)params->c_wall;
 
     // operator data
-    const size_t bytes = lbm::operator_image_bytes(*grid);
+    size_t upload = 0;
+    const size_t bytes = lbm::operator_image_bytes(*grid, &upload);
     auto cleanup = [&]() { lbm_fade_destroy(h); };
     hipError_t e = hipMalloc(&h->opmem, bytes);
     if (e != hipSuccess) {
         cleanup();
         return fail(LBM_ENOMEM, "hipMalloc of operator data failed");
     }
-    std::vector<unsigned char> host(bytes, 0);
+    std::vector<unsigned char> host(upload, 0);
     lbm::build_operator_image(*grid, *params, host.data(), reinterpret_cast<const unsigned char*>(h->opmem), h->ops);
-    e = hipMemcpy(h->opmem, host.data(), bytes, hipMemcpyHostToDevice);
+    e = hipMemcpy(h->opmem, host.data(), upload, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         cleanup();
         return fail(LBM_EDEVICE, std::string("upload of operator data failed: ") + hipGetErrorString(e));
+    }
+    if (bytes > upload) {
+        e = lbm::launch_far_tables(h->ops, d, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // the handle may be used on any stream
+    }
+    if (e != hipSuccess) {
+        cleanup();
+        return fail(LBM_EDEVICE, std::string("far-box operators: ") + hipGetErrorString(e));
     }
     lbm::make_layouts(*grid, h->lays);
     // state

@@ -59,6 +59,7 @@ struct AxisCoeffs {
     std::vector<double> a;   // a_k, k = 0..N (a_0 = 1)
     std::vector<double> cp0; // c+_{0j}, j = 1..N (index j; entry 0 unused)
     std::vector<double> cmN; // c-_{Nj}, j = 0..N-1 (entry N unused)
+    std::vector<double> pg;  // k^gamma, k = 0..N
 };
 AxisCoeffs axis_coeffs(int n, double gamma, double g, double dx);
 // Fractional term of every axis of C into Phi (d consecutive node fields).
@@ -69,10 +70,11 @@ int fade_forward_step(lbm_fade* h, hipStream_t s);
 // Parameter checks of lbm_fade_create (error message set on failure).
 int validate_config(const lbm_grid* grid, int32_t lattice, const lbm_params* params);
 // Operator data of every axis (Toeplitz generator, boundary columns, BF16
-// splits and pair words) as one host image of operator_image_bytes(grid)
-// bytes, built in FP64; ops[mu] receives the device pointers the image has
-// once copied to `base`.
-size_t operator_image_bytes(const lbm_grid& grid);
+// splits and pair words, far-box operators): operator_image_bytes(grid) bytes
+// on the device, of which the first `upload` are a host image built in FP64;
+// launch_far_tables fills the rest once they are copied.  ops[mu] receives
+// the device pointers the data have at `base`.
+size_t operator_image_bytes(const lbm_grid& grid, size_t* upload);
 void build_operator_image(const lbm_grid& grid, const lbm_params& params, unsigned char* host,
                           const unsigned char* base, AxisOp* ops);
 // Strided views of a node field for the operator along each axis.

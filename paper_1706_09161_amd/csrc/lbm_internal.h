@@ -30,15 +30,30 @@ struct AxisOp {
     const uint16_t* gen_lo;
     // Pair words of the split, W(d) = b(d) | b(d - 1) << 16 with b = hi or lo
     // bits (0 for |d| > n - 1), stored with d decreasing: pw[x] = W(pw_top - x)
-    // for x in [0, pw_top + n + 32).  pw_top = 16 ceil((n + 512) / 16) - 1.
+    // for x in [0, pw_top + n + 288).  pw_top = 16 ceil((n + 512) / 16) - 1.
     const uint32_t* pw_hi;
     const uint32_t* pw_lo;
+    // The third plane of T = hi + lo + l3 (same indexing), for the FP32 products
+    // formed from exact three-term splits.
+    const uint32_t* pw_l3;
     int pw_top;
+    // Far part of a long axis (fractional_far.hip; null where it is not used):
+    // operators between boxes, and the interpolation fragments.  T(d) at a
+    // distance |d| >= 64 is far_pos a(d) for d > 0, far_neg a(-d) for d < 0,
+    // a the product-rule weights of gamma = far_g.
+    const uint16_t* far_m;
+    const uint16_t* far_uv;
+    double far_g, far_pos, far_neg;
 };
+
+// Source boxes of 128 nodes of an axis of n nodes (the first starts at -64),
+// rounded up to an even number.
+__host__ __device__ inline int far_sources(int n) { return ((n + 64 + 127) / 128 + 1) & ~1; }
+constexpr size_t kFarUvEntries = 12288;  // BF16 values of the interpolation fragments
 
 // Top index and length of the pair-word arrays of an axis of n nodes.
 inline int pw_top_of(int n) { return 16 * ((n + 512 + 15) / 16) - 1; }
-inline int64_t pw_len_of(int n) { return (int64_t)pw_top_of(n) + n + 32; }
+inline int64_t pw_len_of(int n) { return (int64_t)pw_top_of(n) + n + 288; }
 
 // Workgroup barrier that orders LDS accesses only (release/acquire fences
 // scoped to LDS): global loads in flight stay in flight, unlike
@@ -119,5 +134,15 @@ int64_t big_tiles(const FracLaunch& L);
 // Tile configuration forced through an environment variable (0 = automatic).
 int tile_choice(const char* var);
 hipError_t launch_fractional_bf16x3(FracLaunch& L, hipStream_t s);
+// Long axes (every operator needs its far_m table): near band plus moments of
+// far boxes; terms = 6 (FP32 products) or 3 (3-term split BF16 band).
+// far_used: axis lengths that take this path.  launch_far_tables fills far_m.
+// far_reaches: the kernel's 32-bit byte offsets span the axis.
+bool far_used(int n);
+bool far_reaches(const AxisLayout& lay, int n);
+size_t far_table_entries(int n);
+void far_uv_fill(uint16_t* out, uint16_t (*to_bf16)(double), float (*to_float)(uint16_t));
+hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s);
+hipError_t launch_fractional_far(FracLaunch& L, int terms, hipStream_t s);
 
 }  // namespace lbm
