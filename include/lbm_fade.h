@@ -61,8 +61,8 @@ enum { LBM_D2Q5 = 5, LBM_D3Q7 = 7 };
 enum { LBM_BGK = 0, LBM_MRT = 1 };
 
 /* Arithmetic of the fractional-term GEMM.  Weights are always generated in FP64.
- *   LBM_FP32   FP32 operands and FP32 accumulation, on FP32 MFMA or (long
- *              axes) as exact three-term BF16 splits on BF16 MFMA;
+ *   LBM_FP32   FP32 operands and FP32 accumulation, as exact three-term BF16
+ *              splits on BF16 MFMA, or on FP32 MFMA where that is faster;
  *   LBM_BF16X3 3-term split BF16: W = W_hi + W_lo, C = C_hi + C_lo (round to
  *              nearest even), W_hi C_hi + W_hi C_lo + W_lo C_hi on BF16 MFMA with
  *              FP32 accumulation (the lo*lo term is dropped; the far part of
@@ -156,6 +156,14 @@ LBM_API int lbm_fade_set_diffusion(lbm_fade_t h, const float* D, int32_t on_devi
  * set before every step; the value written by a step is read when that step
  * runs.  NULL goes back to c_wall.  Host input synchronises `stream`. */
 LBM_API int lbm_fade_set_wall(lbm_fade_t h, const float* Cw, int32_t on_device, void* stream);
+
+/* on != 0: the fractional term of axes of at most 768 nodes runs on the
+ * register kernels (FP32 MFMA, or BF16 MFMA for LBM_BF16X3) whatever the grid;
+ * 0 (the default): on the fastest kernel for the grid.  The results differ in
+ * rounding only.  For callers whose results must not change in the last bits
+ * when the choice of kernels does (the autograd wrapper uses it: its gradients
+ * are FP64 values).  May synchronise the device. */
+LBM_API int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on);
 
 /* Advance n >= 0 time steps.  Asynchronous; the launches of one step are: the
  * fractional-term GEMM of every axis, then the fused collide-stream-boundary-

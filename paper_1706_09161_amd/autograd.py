@@ -38,6 +38,7 @@ class FadeSolve(torch.autograd.Function):
         kw = {k: v for k, v in opts.items() if k not in ("alpha", "steps", "ckpt_every")}
         solver = LbmFade(dim, n, alpha=opts["alpha"], p=_vals(p), D=Dm, u=_vals(u), **kw)
         try:
+            solver.set_register_kernels(True)  # the FP64 gradients keep their last bits
             solver.set_C(C0.detach().float().contiguous())
             solver.set_source(None if S is None else S.detach().float().contiguous())
             solver.step(opts["steps"])

@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbmfade.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["lbm_fade.hip", "fractional_gemm.hip", "fractional_gemm_bf16.hip", "fractional_far.hip", "collide_stream.hip", "adjoint.hip",
+SOURCES = ["lbm_fade.hip", "fractional_gemm.hip", "fractional_gemm_bf16.hip", "fractional_split.hip", "fractional_far.hip", "collide_stream.hip", "adjoint.hip",
            "random_walk.hip", "apply_phi_noalloc.hip"]
 ARCH = "gfx950"
 

@@ -102,7 +102,7 @@ extern "C" int lbm_fade_apply_phi_noalloc(const lbm_grid* grid, const lbm_params
     if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("upload of operator data: ") + hipGetErrorString(e));
     e = lbm::launch_far_tables(ops, grid->dim, s);
     if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("far-box operators: ") + hipGetErrorString(e));
-    e = lbm::launch_fractional(ops, lays, grid->dim, params->precision, C, 0, Phi, nodes, s);
+    e = lbm::launch_fractional(ops, lays, grid->dim, params->precision, false, C, 0, Phi, nodes, s);
     if (e != hipSuccess) return fail(LBM_EDEVICE, std::string("fractional term: ") + hipGetErrorString(e));
     return LBM_OK;
 }

@@ -79,43 +79,6 @@ __device__ __forceinline__ void six16(const Frag3& a, const Frag3& b, f32x4& mai
     corr = mfma16(a.h, b.m, corr);
 }
 
-__device__ __forceinline__ bf16x8 ld16(const uint16_t* p) { return as_bf16(*reinterpret_cast<const u32x4*>(p)); }
-
-// C of a line block through a buffer descriptor: a load past its end (or at
-// a negative k) returns zero or a neighbouring line's value and never faults,
-// so ragged ends need no separate code, only a mask on k.
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-
-__device__ __forceinline__ float ldf(Rsrc r, uint32_t boff)
-{
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, boff, 0, 0));
-}
-
-// 8 consecutive k of a line from byte offset boff (ks4: bytes between k)
-template <bool CONTIG>
-__device__ __forceinline__ void load8(Rsrc r, uint32_t boff, uint32_t ks4, float (&v)[8])
-{
-    if constexpr (CONTIG) {
-        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, boff, 0, 0);
-        const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, boff + 16, 0, 0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v[e] = __uint_as_float(a[e]);
-            v[4 + e] = __uint_as_float(b[e]);
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = ldf(r, boff + (uint32_t)e * ks4);
-    }
-}
-
-// v[e] = 0 unless k_lo <= k + e < k_hi
-__device__ __forceinline__ void mask8(float (&v)[8], int k, int k_lo, int k_hi)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (unsigned)(k + e - k_lo) < (unsigned)(k_hi - k_lo) ? v[e] : 0.f;
-}
-
 template <bool CONTIG, int NW, int NT>
 __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay, const float* __restrict__ C,
                                          float* __restrict__ Phi, int tiles_l, int splits, int bid, int total,
@@ -265,21 +228,8 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
     // the two wavefronts of a SIMD (wave, wave + 4) take different halves: the
     // halves of a one-sided operator's band differ in length
     const int half = (wave ^ (wave >> 2)) & 1;
-    // Toeplitz fragment for step s of the band and output block c
-    const int mbase = 127 - 64 * half - li + 8 * lh;
-    auto load_t = [&](int s, int c, Frag3& f) {
-        const uint32_t* w = win + mbase + 16 * s - 32 * c;
-        u32x4 h, m, l;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            h[p] = w[2 * p];
-            m[p] = w[kWin + 2 * p];
-            if constexpr (NT == 6) l[p] = w[2 * kWin + 2 * p];
-        }
-        f.h = as_bf16(h);
-        f.m = as_bf16(m);
-        if constexpr (NT == 6) f.l = as_bf16(l);
-    };
+    // word of the Toeplitz fragment of step s and output block c: wbase + 16 s - 32 c
+    const uint32_t* wbase = win + 127 - 64 * half - li + 8 * lh;
 
     for (int g = g_lo; g < g_hi; ++g) {
         const int J = NB * g + (wave >> 1);  // this wavefront's target box (may lie past the axis)
@@ -296,13 +246,6 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
         const uint32_t band_off = line_off + (uint32_t)(kband + 8 * lh) * ks4;
         auto load_c = [&](int s, float (&v)[8]) {
             load8<CONTIG>(Cr, band_off + (uint32_t)(16 * min(s, s_hi - 1)) * ks4, ks4, v);
-        };
-        auto planes = [&](const float (&v)[8], Frag3& f) {
-            u32x4 h, m, l;
-            split3_8(v, h, m, l);
-            f.h = as_bf16(h);
-            f.m = as_bf16(m);
-            f.l = as_bf16(l);
         };
         float raw[2][8];
         if (live) {
@@ -369,53 +312,29 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
         if (!live) continue;
 
         // ---- band: C split in registers, its loads 2 steps ahead
-        f32x16 main_[2][2], corr[2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) main_[0][c][r] = main_[1][c][r] = corr[c][r] = 0.f;
+        Accumulators<CONTIG, NT> acc;
+        acc.clear();
         Frag3 cf[2], tf[4];  // tf: block-0 fragments by step modulo 4; block 1 of step s is block 0 of step s - 2
-        load_t(s_lo, 1, tf[2]);
-        load_t(s_lo + 1, 1, tf[3]);
-        load_t(s_lo, 0, tf[0]);
+        tf[2] = toeplitz<NT>(wbase + 16 * s_lo - 32, kWin);
+        tf[3] = toeplitz<NT>(wbase + 16 * s_lo - 16, kWin);
+        tf[0] = toeplitz<NT>(wbase + 16 * s_lo, kWin);
         const int kl = kband + 8 * lh;
         const bool edge = kband + 16 * s_lo < k_lo || kband + 16 * s_hi > k_hi;  // uniform
         if (edge) mask8(raw[0], kl + 16 * s_lo, k_lo, k_hi);
-        planes(raw[0], cf[0]);
-        auto six32 = [&](const Frag3& x, const Frag3& y0, const Frag3& y1, f32x16 (&m)[2]) {
-            if constexpr (NT == 6) {
-                corr[0] = mfma32<CONTIG>(x.l, y0.h, corr[0]);
-                corr[1] = mfma32<CONTIG>(x.l, y1.h, corr[1]);
-            }
-            m[0] = mfma32<CONTIG>(x.h, y0.h, m[0]);
-            if constexpr (NT == 6) {
-                corr[0] = mfma32<CONTIG>(x.h, y0.l, corr[0]);
-                corr[1] = mfma32<CONTIG>(x.h, y1.l, corr[1]);
-            }
-            m[1] = mfma32<CONTIG>(x.h, y1.h, m[1]);
-            if constexpr (NT == 6) {
-                corr[0] = mfma32<CONTIG>(x.m, y0.m, corr[0]);
-                corr[1] = mfma32<CONTIG>(x.m, y1.m, corr[1]);
-            }
-            corr[0] = mfma32<CONTIG>(x.m, y0.h, corr[0]);
-            corr[1] = mfma32<CONTIG>(x.m, y1.h, corr[1]);
-            corr[0] = mfma32<CONTIG>(x.h, y0.m, corr[0]);
-            corr[1] = mfma32<CONTIG>(x.h, y1.m, corr[1]);
-        };
+        cf[0] = planes(raw[0]);
         for (int s = s_lo; s < s_hi; s += 4) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (edge) mask8(raw[(u + 1) & 1], kl + 16 * (s + u + 1), k_lo, k_hi);
-                load_t(min(s + u + 1, 15), 0, tf[(u + 1) & 3]);
+                tf[(u + 1) & 3] = toeplitz<NT>(wbase + 16 * min(s + u + 1, 15), kWin);
                 load_c(s + u + 2, raw[u & 1]);  // slot of step s + u, converted already
-                planes(raw[(u + 1) & 1], cf[(u + 1) & 1]);
-                six32(cf[u & 1], tf[u & 3], tf[(u + 2) & 3], main_[u & 1]);
+                cf[(u + 1) & 1] = planes(raw[(u + 1) & 1]);
+                acc.add(cf[u & 1], tf[u & 3], tf[(u + 2) & 3], u & 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 
         // ---- far part: both wavefronts' local coefficients times l_p(j)
-        f32x16 acc[2];
         {
             Frag3 uf[2];
 #pragma unroll
@@ -439,78 +358,14 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
                 l[p] = qp;
             }
             const Frag3 x = {as_bf16(h), as_bf16(m), as_bf16(l)};
-            // always six products
-#pragma unroll
-            for (int c = 0; c < 2; ++c) corr[c] = mfma32<CONTIG>(x.l, uf[c].h, corr[c]);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) main_[1][c] = mfma32<CONTIG>(x.h, uf[c].h, main_[1][c]);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) corr[c] = mfma32<CONTIG>(x.h, uf[c].l, corr[c]);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) corr[c] = mfma32<CONTIG>(x.m, uf[c].m, corr[c]);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) corr[c] = mfma32<CONTIG>(x.m, uf[c].h, corr[c]);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) corr[c] = mfma32<CONTIG>(x.h, uf[c].m, corr[c]);
+            acc.add6(x, uf[0], uf[1], 1);
         }
-        bool odd = false;
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                acc[c][r] = (main_[0][c][r] + main_[1][c][r]) + corr[c][r];
-                odd = odd || not_finite(acc[c][r]);
-            }
-        const bool any_odd = NT == 6 && __any(odd);
 
         // ---- boundary columns and stores
-        const float* cw = cols + wave * 128;
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int row = 8 * r4 + 4 * lh;  // first of 4 accumulator rows; columns are li
-                f32x4 x0, xN, y0, yN;  // boundary weights, wall values
-                if constexpr (CONTIG) {
-                    x0 = cw[32 * c + li];
-                    xN = cw[64 + 32 * c + li];
-                    y0 = *reinterpret_cast<const f32x4*>(w0s + row);
-                    yN = *reinterpret_cast<const f32x4*>(wNs + row);
-                } else {
-                    x0 = *reinterpret_cast<const f32x4*>(cw + 32 * c + row);
-                    xN = *reinterpret_cast<const f32x4*>(cw + 64 + 32 * c + row);
-                    y0 = b0;
-                    yN = bN;
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int line = CONTIG ? row + e : li;
-                    const int j = jw + 32 * c + (CONTIG ? li : row + e);
-                    if (line < nl && j < n) {
-                        float v = acc[c][4 * r4 + e];
-                        v = fmaf(x0[e], y0[e], v);
-                        v = fmaf(xN[e], yN[e], v);
-                        *reinterpret_cast<float*>(reinterpret_cast<char*>(Pb) + (uint32_t)line * ls4 + (uint32_t)j * ks4) = v;
-                    }
-                }
-            }
-        // outputs whose split sum is not finite: again, from the definition
-        if (any_odd) {
-#pragma unroll 1
-            for (int o = 0; o < 32; ++o) {
-                const int row = 8 * ((o >> 2) & 3) + 4 * lh + (o & 3), col = 32 * (o >> 4);
-                const int line = CONTIG ? row : li, jl = col + (CONTIG ? li : row), j = jw + jl;
-                if (line >= nl || j >= n) continue;
-                float* out = reinterpret_cast<float*>(reinterpret_cast<char*>(Pb) + (uint32_t)line * ls4 + (uint32_t)j * ks4);
-                if (!not_finite(*out)) continue;
-                const float* c = reinterpret_cast<const float*>(reinterpret_cast<const char*>(Cb) + (uint32_t)line * ls4);
-                const int64_t ks = CONTIG ? 1 : js;
-                float v = plain_sum(op.gen + N, op.upper_only ? max(k_lo, j) : k_lo,
-                                    op.lower_only ? min(k_hi, j + 1) : k_hi, c, ks, j);
-                v = fmaf(cw[jl], c[0], v);
-                *out = fmaf(cw[64 + jl], c[(int64_t)N * ks], v);
-            }
-        }
+        f32x16 sum[2];
+        acc.total(sum);
+        store_tile<CONTIG, NT == 6>(op, sum, 0, 8, {cols + wave * 128, w0s, wNs, b0, bN}, Cb, Pb, nl, jw, k_lo, k_hi,
+                                    ls4, ks4);
     }
 }
 
@@ -642,10 +497,11 @@ bool far_reaches(const AxisLayout& lay, int n)
 
 bool far_used(int n)
 {
-    // Upper end: the moments of 32 lines (16 n BF16 triples per 128 nodes) fill
-    // the LDS.  Lower end: there the band and the two box steps cost as much as
-    // the dense sum (512^2 two-sided: dense 9.6 us).
-    return n >= 640 && n <= 4096;
+    // Upper end: the moments of 32 lines (16 BF16 triples per 128 nodes and
+    // line) fill the LDS.  Lower end: there the band and the two box steps cost
+    // as much as the dense sum (FP32, far / dense, us: 640^2 16.4 / 12.9, 768^2
+    // 17.9 / 18.5, 896 x 900 18.4 / 24.2, 1024^2 19.3 / 26.0).
+    return n > 768 && n <= 4096;
 }
 
 size_t far_table_entries(int n) { return (size_t)((n + kBox - 1) / kBox + far_sources(n) - 1) * 3 * kRank * kRank; }

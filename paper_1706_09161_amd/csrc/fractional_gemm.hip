@@ -910,11 +910,12 @@ hipError_t run_f32_ring(FracLaunch& L, hipStream_t s)
 
 namespace {
 hipError_t run_f32_auto(FracLaunch& L, hipStream_t s);
-hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, hipStream_t s);
+hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register_kernels, hipStream_t s);
 }
 
-hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision, const float* C,
-                             int64_t in_stride, float* Phi, int64_t nodes, hipStream_t s)
+hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision,
+                             bool register_kernels, const float* C, int64_t in_stride, float* Phi, int64_t nodes,
+                             hipStream_t s)
 {
     if (precision == 2) {
         for (int a = 0; a < naxes; ++a) {
@@ -939,7 +940,7 @@ hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxe
         L.Phi[a] = Phi + a * nodes;
     }
     const bool forced = tile_choice(precision == 1 ? "LBM_BF16_TILE" : "LBM_FP32_TILE") != 0;
-    return launch_by_length(L, precision == 1, forced, s);
+    return launch_by_length(L, precision == 1, forced, register_kernels, s);
 }
 
 hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, const float* const* C, float* const* Phi,
@@ -955,24 +956,27 @@ hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, cons
         L.C[a] = C[a];
         L.Phi[a] = Phi[a];
     }
-    return launch_by_length(L, false, tile_choice("LBM_FP32_TILE") != 0, s);
+    return launch_by_length(L, false, tile_choice("LBM_FP32_TILE") != 0, true, s);
 }
 
 namespace {
 
 // The axes that have their far-box operators go to that kernel, the others to
 // the dense kernels: one launch where all axes are of a kind.  Split BF16: up
-// to 1100 nodes only where the dense kernel lacks its 16-wide steps (801 x 650
-// 22.8 us dense, 17.6 far; 1024^2 17.7 dense, 19.2 far; 2048^2 103, 42).
-hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, hipStream_t s)
+// to 1024 nodes only beyond 896 and where the dense register kernel lacks its
+// 16-wide steps (896 x 900: 17.2 us far, 17.6 dense; 1024^2 18.3, 16.5).
+hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register_kernels, hipStream_t s)
 {
-    auto dense = [&](FracLaunch& D) { return bf16 ? launch_fractional_bf16x3(D, s) : run_f32_auto(D, s); };
+    auto dense = [&](FracLaunch& D) {
+        if (!forced && !register_kernels && split_takes(D, bf16 ? 3 : 6)) return launch_fractional_split(D, bf16 ? 3 : 6, s);
+        return bf16 ? launch_fractional_bf16x3(D, s) : run_f32_auto(D, s);
+    };
     FracLaunch F, D;
     memset(&F, 0, sizeof(F));
     memset(&D, 0, sizeof(D));
     for (int a = 0; a < L.naxes; ++a) {
         const int n = L.op[a].n;
-        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && (!bf16 || n > 1100 || n % 16 != 0);
+        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && (!bf16 || n > 1024 || (n > 896 && n % 16 != 0));
         FracLaunch& X = far ? F : D;
         X.op[X.naxes] = L.op[a];
         X.lay[X.naxes] = L.lay[a];

@@ -818,9 +818,9 @@ __global__ __launch_bounds__(kThreads, NBJ <= 4 ? 2 : 1) void fractional_bf16x3_
     while (axis + 1 < L.naxes && bid >= L.first[axis + 1]) ++axis;
     const int local = bid - L.first[axis];
     const int total = L.first[axis + 1] - L.first[axis];
-    if (L.lay[axis].contiguous)
-        bf16x3_ring_tile<true, NBJ, WL, KSPLIT, P, VEC_X, KFULL>(L.op[axis], L.lay[axis], L.C[axis], L.Phi[axis],
-                                                          L.tiles_m[axis], L.tiles_n[axis], local, total, smem_r);
+    if (axis == 0 && L.lay[0].contiguous)
+        bf16x3_ring_tile<true, NBJ, WL, KSPLIT, P, VEC_X, KFULL>(L.op[0], L.lay[0], L.C[0], L.Phi[0], L.tiles_m[0],
+                                                          L.tiles_n[0], local, total, smem_r);
     else
         bf16x3_ring_tile<false, NBJ, WL, KSPLIT, P, false, KFULL>(L.op[axis], L.lay[axis], L.C[axis],
                                                            L.Phi[axis], L.tiles_m[axis], L.tiles_n[axis], local, total,

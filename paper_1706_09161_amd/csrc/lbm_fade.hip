@@ -345,7 +345,8 @@ int check_device(lbm_fade* h)
 
 int run_phi(lbm_fade* h, const float* C, float* Phi, hipStream_t s)
 {
-    HIP_TRY(lbm::launch_fractional(h->ops, h->lays, h->dim, h->params.precision, C, 0, Phi, h->nodes, s));
+    HIP_TRY(lbm::launch_fractional(h->ops, h->lays, h->dim, h->params.precision, h->register_kernels, C, 0, Phi,
+                                   h->nodes, s));
     return LBM_OK;
 }
 
@@ -554,9 +555,9 @@ size_t operator_image_bytes(const lbm_grid& grid, size_t* upload)
         const size_t n = (size_t)grid.n[mu];
         bytes += r256(sizeof(float) * (2 * n - 1)) + 2 * r256(sizeof(float) * n) +
                  2 * r256(sizeof(uint16_t) * (2 * n - 1)) + 2 * r256(sizeof(uint32_t) * pw_len_of((int)n));
+        if (n <= kThirdPlaneMax) bytes += r256(sizeof(uint32_t) * pw_len_of((int)n));
         if (far_used((int)n)) {
             far = true;
-            bytes += r256(sizeof(uint32_t) * pw_len_of((int)n));
             tables += r256(sizeof(uint16_t) * far_table_entries((int)n));
         }
     }
@@ -595,8 +596,8 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         op.lower_only = P.p[mu] == 1.0;
         op.upper_only = P.p[mu] == 0.0;
         op.ends_excluded = 1;
-        const bool third = far_used(n);
-        far = far || third;
+        const bool third = n <= kThirdPlaneMax;
+        far = far || far_used(n);
         const size_t og = carve(sizeof(float) * (2 * n - 1));
         const size_t o0 = carve(sizeof(float) * n);
         const size_t oN = carve(sizeof(float) * n);
@@ -885,6 +886,19 @@ int lbm_fade_set_wall(lbm_fade_t h, const float* Cw, int32_t on_device, void* st
     HIP_TRY(hipMemcpyAsync(h->Cw, Cw, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));
     h->var_wall = true;
+    return LBM_OK;
+}
+
+int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on)
+{
+    if (!h) return fail(LBM_EINVAL, "null handle");
+    int rc = check_device(h);
+    if (rc) return rc;
+    if (h->register_kernels != (on != 0) && h->gexec) {
+        HIP_TRY(hipDeviceSynchronize());  // a replay may be running
+        drop_graph(h);
+    }
+    h->register_kernels = on != 0;
     return LBM_OK;
 }
 

@@ -28,6 +28,7 @@ struct lbm_fade {
     float* Cw = nullptr;          // Dirichlet value of every node
     bool var_D = false;           // dB set by lbm_fade_set_diffusion (else zero)
     bool var_wall = false;        // Cw set by lbm_fade_set_wall (else c_wall)
+    bool register_kernels = false;  // dense axes on the register kernels (lbm_fade_set_register_kernels)
     void* opmem = nullptr;  // generators, corrections and BF16 splits of all axes
     int* flag = nullptr;
     lbm::AxisOp ops[3];

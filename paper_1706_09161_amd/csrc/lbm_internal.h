@@ -34,7 +34,7 @@ struct AxisOp {
     const uint32_t* pw_hi;
     const uint32_t* pw_lo;
     // The third plane of T = hi + lo + l3 (same indexing), for the FP32 products
-    // formed from exact three-term splits.
+    // formed from exact three-term splits; null on axes beyond kThirdPlaneMax.
     const uint32_t* pw_l3;
     int pw_top;
     // Far part of a long axis (fractional_far.hip; null where it is not used):
@@ -50,6 +50,8 @@ struct AxisOp {
 // rounded up to an even number.
 __host__ __device__ inline int far_sources(int n) { return ((n + 64 + 127) / 128 + 1) & ~1; }
 constexpr size_t kFarUvEntries = 12288;  // BF16 values of the interpolation fragments
+
+constexpr int kThirdPlaneMax = 4096;
 
 // Top index and length of the pair-word arrays of an axis of n nodes.
 inline int pw_top_of(int n) { return 16 * ((n + 512 + 15) / 16) - 1; }
@@ -110,9 +112,11 @@ struct CollideConsts {
 
 // Kernel launchers (host functions).  All return a hipError_t.
 // Fractional term of all axes: axis a reads C + a * in_stride (in_stride = 0:
-// one field for every axis) and writes Phi + a * nodes.
-hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision, const float* C,
-                             int64_t in_stride, float* Phi, int64_t nodes, hipStream_t s);
+// one field for every axis) and writes Phi + a * nodes.  register_kernels: the
+// axes without boxes stay on the register kernels.
+hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision,
+                             bool register_kernels, const float* C, int64_t in_stride, float* Phi, int64_t nodes,
+                             hipStream_t s);
 // FP32 only: nops (<= kMaxOps) operators with their own layouts, inputs and
 // outputs, in one launch.
 hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, const float* const* C, float* const* Phi,
@@ -134,6 +138,10 @@ int64_t big_tiles(const FracLaunch& L);
 // Tile configuration forced through an environment variable (0 = automatic).
 int tile_choice(const char* var);
 hipError_t launch_fractional_bf16x3(FracLaunch& L, hipStream_t s);
+// Dense kernel on the BF16 matrix cores; terms as below.  split_takes: the
+// launches it is used for.
+bool split_takes(const FracLaunch& L, int terms);
+hipError_t launch_fractional_split(FracLaunch& L, int terms, hipStream_t s);
 // Long axes (every operator needs its far_m table): near band plus moments of
 // far boxes; terms = 6 (FP32 products) or 3 (3-term split BF16 band).
 // far_used: axis lengths that take this path.  launch_far_tables fills far_m.

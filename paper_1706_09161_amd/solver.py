@@ -191,6 +191,11 @@ class LbmFade:
         ptr, dev, keep = self._in(Cw, self.nodes)
         L.check(L.lib().lbm_fade_set_wall(self._h, ptr, dev, _stream_ptr(stream)))
 
+    def set_register_kernels(self, on: bool):
+        """Keep axes of at most 768 nodes on the register kernels of the
+        fractional term (results then do not depend on the kernel selection)."""
+        L.check(L.lib().lbm_fade_set_register_kernels(self._h, int(bool(on))))
+
     def step(self, n: int = 1, stream=None):
         L.check(L.lib().lbm_fade_step(self._h, int(n), _stream_ptr(stream)))
 

@@ -1,7 +1,8 @@
 """The fractional term of long axes (near band plus moments of far boxes) at
-the sizes where it can go wrong: the shortest and longest axes that take it,
-ends of boxes and chunks, ragged ends, few lines, every axis of a grid, one-
-and two-sided operators; and lines that hold infinities or NaN.
+the sizes where it can go wrong: the longest dense axes and the shortest and
+longest ones beyond, ends of boxes, ragged ends, few lines, every axis of a
+grid, a long axis beside a short one, one- and two-sided operators; and lines
+that hold infinities or NaN.
 
 FP32 tolerance, relative to sum_k |K_jk| |C_k| (the value itself: C and every
 weight are >= 0): an accumulator of the band is rounded 8 times and the three
@@ -28,14 +29,16 @@ CASES = [
     (2, [35, 641], [1.5, 1.2], [0.5, 0.8]),
     (2, [703, 768], [1.05, 1.95], [1.0, 0.0]),
     (2, [769, 1023], [1.7, 1.4], [0.0, 1.0]),
+    (2, [770, 895], [1.4, 1.6], [0.3, 0.0]),
+    (2, [900, 832], [1.6, 1.3], [1.0, 0.6]),
     (2, [1025, 33], [1.2, 1.5], [0.6, 0.5]),
     (2, [3, 1153], [1.5, 1.6], [0.5, 1.0]),
     (2, [1216, 650], [1.9, 1.1], [0.4, 0.0]),
     (2, [4096, 5], [1.2, 1.5], [0.7, 0.5]),
     (2, [40, 4095], [1.5, 1.4], [0.5, 0.0]),
-    (3, [9, 655, 4], [1.5, 1.3, 1.5], [0.5, 0.3, 0.5]),
+    (3, [9, 855, 4], [1.5, 1.3, 1.5], [0.5, 0.3, 0.5]),
     (3, [5, 7, 1100], [1.5, 1.5, 1.8], [0.5, 0.5, 0.9]),
-    (3, [666, 5, 4], [2.0, 1.5, 1.5], [0.5, 0.5, 0.5]),
+    (3, [866, 5, 4], [2.0, 1.5, 1.5], [0.5, 0.5, 0.5]),
 ]
 
 
@@ -72,16 +75,17 @@ def test_long_axes_match_oracle(case, precision):
 
 @pytest.mark.parametrize("p", [[0.4, 0.5], [1.0, 0.5], [0.0, 0.5]], ids=["two-sided", "left", "right"])
 @pytest.mark.parametrize("axis", [0, 1])
-def test_lines_with_infinities_and_nan(axis, p):
-    """One line with +inf, one with -inf, one with NaN at node 333 of a
-    700-node axis: the outputs whose integral reaches the node take its value
+@pytest.mark.parametrize("size", [70, 700, 900])
+def test_lines_with_infinities_and_nan(size, axis, p):
+    """One line with +inf, one with -inf, one with NaN at an inner node, on
+    dense axes and one with boxes: the outputs whose integral reaches the node take its value
     (every weight is > 0) and every other output is that of the finite field."""
-    n, at = [700, 40], 333
+    n, at = [size, 40], size // 2 - 17
     pa = list(p)
     if axis == 1:
         n, pa = n[::-1], pa[::-1]
     cfg = synth.small(2, n, alpha=[1.4, 1.4], p=pa, seed=52)
-    C = np.random.default_rng(24).uniform(0.5, 1.0, (40, 700)).astype(np.float32)  # [line, node]
+    C = np.random.default_rng(24).uniform(0.5, 1.0, (40, size)).astype(np.float32)  # [line, node]
     bad = C.copy()
     for line, v in ((3, np.inf), (17, -np.inf), (38, np.nan)):
         bad[line, at] = v
@@ -94,8 +98,8 @@ def test_lines_with_infinities_and_nan(axis, p):
         got = s.apply_phi(torch.from_numpy(lay(bad)).cuda())[axis].cpu().numpy()
     if axis == 1:
         good, got = good.T, got.T
-    j = np.arange(700)
-    reach = np.ones(700, bool) if 0 < p[0] < 1 else (j >= at if p[0] == 1.0 else j <= at)
+    j = np.arange(size)
+    reach = np.ones(size, bool) if 0 < p[0] < 1 else (j >= at if p[0] == 1.0 else j <= at)
     for line in range(40):
         want = good[line].copy()
         if line in (3, 17, 38):
