@@ -65,8 +65,7 @@ enum { LBM_BGK = 0, LBM_MRT = 1 };
  *              splits on BF16 MFMA, or on FP32 MFMA where that is faster;
  *   LBM_BF16X3 3-term split BF16: W = W_hi + W_lo, C = C_hi + C_lo (round to
  *              nearest even), W_hi C_hi + W_hi C_lo + W_lo C_hi on BF16 MFMA with
- *              FP32 accumulation (the lo*lo term is dropped; the far part of
- *              long axes is formed as for LBM_FP32);
+ *              FP32 accumulation (the lo*lo term is dropped);
  *   LBM_FP32_SIMT  FP32 fused multiply-add on the vector units (no MFMA); a
  *              plain kernel kept as a second implementation of the operator. */
 enum { LBM_FP32 = 0, LBM_BF16X3 = 1, LBM_FP32_SIMT = 2 };

@@ -72,7 +72,7 @@ extern "C" int lbm_fade_apply_phi_noalloc(const lbm_grid* grid, const lbm_params
     if (rc) return rc;
     const int64_t nodes = (int64_t)grid->n[0] * grid->n[1] * (grid->dim == 3 ? grid->n[2] : 1);
     size_t upload = 0;
-    const size_t op_bytes = lbm::operator_image_bytes(*grid, &upload);
+    const size_t op_bytes = lbm::operator_image_bytes(*grid, *params, &upload);
     size_t need = 0;
     for (int mu = 0; mu < grid->dim; ++mu) need += axis_need((size_t)grid->n[mu]);
     if (need > kScratchBytes || op_bytes > kScratchBytes + kMoreBytes)

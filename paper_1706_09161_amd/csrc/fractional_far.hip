@@ -28,16 +28,15 @@
 // workgroups share a line block's target boxes and each computes the moments
 // again.  Each wavefront reads the C of its band straight into registers and
 // splits it there; a group has one barrier, between the two wavefronts' halves
-// of the local coefficients and their use.  NT = 6 forms FP32 products
-// (LBM_FP32); NT = 3 forms the band with the 3-term split of LBM_BF16X3.  The
-// far part is always formed with six products.
+// of the local coefficients and their use.  LBM_FP32 only: in LBM_BF16X3 the
+// rounding of the split weights, which this sum does not have, is the result's
+// largest error, so its values would be other ones (4096^2, 10 steps: C moves
+// by up to 1.2e-3 of its rms, as far as it is from 64 bits).
 //
-// Measured (us per launch, both axes, graph replay; before: the dense FP32 or
-// split-BF16 kernels), one-sided p = (1, 0) / two-sided p = (0.3, 0.8):
-//   FP32        4096^2 1113 / 2106 -> 118 / 158, 2048^2 183 / 272 -> 39 / 48,
-//               1024^2 39 / 41 -> 18 / 21, 801 x 650 35 / 37 -> 16 / 19;
-//   split BF16  4096^2 308 / 541 -> 102 / 139, 2048^2 71 / 103 -> 36 / 42,
-//               801 x 650 22 / 23 -> 14 / 18.
+// Measured (us per launch, both axes, graph replay; before: the dense FP32
+// kernels), one-sided p = (1, 0) / two-sided p = (0.3, 0.8): 4096^2 1113 / 2106
+// -> 118 / 158, 2048^2 183 / 272 -> 39 / 48, 1024^2 39 / 41 -> 18 / 21,
+// 801 x 650 35 / 37 -> 16 / 19.
 // At 4096^2 the moments read C at 7 TB/s; of the band's time half is matrix
 // work, the rest the split of C, its loads and the stores.  Below about 1500
 // nodes one wavefront per SIMD runs load, moments, local coefficients and band
@@ -79,7 +78,7 @@ __device__ __forceinline__ void six16(const Frag3& a, const Frag3& b, f32x4& mai
     corr = mfma16(a.h, b.m, corr);
 }
 
-template <bool CONTIG, int NW, int NT>
+template <bool CONTIG, int NW>
 __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay, const float* __restrict__ C,
                                          float* __restrict__ Phi, int tiles_l, int splits, int bid, int total,
                                          unsigned char* smem)
@@ -312,12 +311,12 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
         if (!live) continue;
 
         // ---- band: C split in registers, its loads 2 steps ahead
-        Accumulators<CONTIG, NT> acc;
+        Accumulators<CONTIG, 6> acc;
         acc.clear();
         Frag3 cf[2], tf[4];  // tf: block-0 fragments by step modulo 4; block 1 of step s is block 0 of step s - 2
-        tf[2] = toeplitz<NT>(wbase + 16 * s_lo - 32, kWin);
-        tf[3] = toeplitz<NT>(wbase + 16 * s_lo - 16, kWin);
-        tf[0] = toeplitz<NT>(wbase + 16 * s_lo, kWin);
+        tf[2] = toeplitz<6>(wbase + 16 * s_lo - 32, kWin);
+        tf[3] = toeplitz<6>(wbase + 16 * s_lo - 16, kWin);
+        tf[0] = toeplitz<6>(wbase + 16 * s_lo, kWin);
         const int kl = kband + 8 * lh;
         const bool edge = kband + 16 * s_lo < k_lo || kband + 16 * s_hi > k_hi;  // uniform
         if (edge) mask8(raw[0], kl + 16 * s_lo, k_lo, k_hi);
@@ -326,7 +325,7 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (edge) mask8(raw[(u + 1) & 1], kl + 16 * (s + u + 1), k_lo, k_hi);
-                tf[(u + 1) & 3] = toeplitz<NT>(wbase + 16 * min(s + u + 1, 15), kWin);
+                tf[(u + 1) & 3] = toeplitz<6>(wbase + 16 * min(s + u + 1, 15), kWin);
                 load_c(s + u + 2, raw[u & 1]);  // slot of step s + u, converted already
                 cf[(u + 1) & 1] = planes(raw[(u + 1) & 1]);
                 acc.add(cf[u & 1], tf[u & 3], tf[(u + 2) & 3], u & 1);
@@ -358,18 +357,18 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
                 l[p] = qp;
             }
             const Frag3 x = {as_bf16(h), as_bf16(m), as_bf16(l)};
-            acc.add6(x, uf[0], uf[1], 1);
+            acc.add(x, uf[0], uf[1], 1);
         }
 
         // ---- boundary columns and stores
         f32x16 sum[2];
         acc.total(sum);
-        store_tile<CONTIG, NT == 6>(op, sum, 0, 8, {cols + wave * 128, w0s, wNs, b0, bN}, Cb, Pb, nl, jw, k_lo, k_hi,
+        store_tile<CONTIG, true>(op, sum, 0, 8, {cols + wave * 128, w0s, wNs, b0, bN}, Cb, Pb, nl, jw, k_lo, k_hi,
                                     ls4, ks4);
     }
 }
 
-template <int NW, int NT>
+template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void fractional_far(FracLaunch L)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_f[];
@@ -379,10 +378,10 @@ __global__ __launch_bounds__(64 * NW, 2) void fractional_far(FracLaunch L)
     const int local = bid - L.first[axis];
     const int total = L.first[axis + 1] - L.first[axis];
     if (L.lay[axis].contiguous)
-        far_tile<true, NW, NT>(L.op[axis], L.lay[axis], L.C[axis], L.Phi[axis], L.tiles_m[axis], L.tiles_n[axis], local,
+        far_tile<true, NW>(L.op[axis], L.lay[axis], L.C[axis], L.Phi[axis], L.tiles_m[axis], L.tiles_n[axis], local,
                                total, smem_f);
     else
-        far_tile<false, NW, NT>(L.op[axis], L.lay[axis], L.C[axis], L.Phi[axis], L.tiles_m[axis], L.tiles_n[axis],
+        far_tile<false, NW>(L.op[axis], L.lay[axis], L.C[axis], L.Phi[axis], L.tiles_m[axis], L.tiles_n[axis],
                                 local, total, smem_f);
 }
 
@@ -438,7 +437,7 @@ __global__ __launch_bounds__(256) void far_table(FarTables F)
     }
 }
 
-template <int NW, int NT>
+template <int NW>
 size_t far_lds(int n)
 {
     const int ms = kRank * far_sources(n) + 8;
@@ -446,7 +445,7 @@ size_t far_lds(int n)
            sizeof(uint16_t) * (6144 + 3 * 32 * ms);
 }
 
-template <int NW, int NT>
+template <int NW>
 hipError_t run_far(FracLaunch& L, hipStream_t s)
 {
     size_t lds = 0;
@@ -455,7 +454,7 @@ hipError_t run_far(FracLaunch& L, hipStream_t s)
         const AxisLayout& lay = L.lay[a];
         L.tiles_m[a] = (int)((lay.lines + 31) / 32);
         per[a] = (int64_t)L.tiles_m[a] * (lay.contiguous ? 1 : lay.batches);
-        const size_t b = far_lds<NW, NT>(L.op[a].n);
+        const size_t b = far_lds<NW>(L.op[a].n);
         lds = b > lds ? b : lds;
     }
     // groups per workgroup: the fewest that keep the launch within one round of
@@ -478,7 +477,7 @@ hipError_t run_far(FracLaunch& L, hipStream_t s)
     }
     if (grid > 0x7fffffff || lds > 160 * 1024) return hipErrorInvalidValue;
     L.first[L.naxes] = (int)grid;
-    auto kern = fractional_far<NW, NT>;
+    auto kern = fractional_far<NW>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -554,15 +553,14 @@ hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fractional_far(FracLaunch& L, int terms, hipStream_t s)
+hipError_t launch_fractional_far(FracLaunch& L, hipStream_t s)
 {
     int nmax = 0;
     for (int a = 0; a < L.naxes; ++a) nmax = L.op[a].n > nmax ? L.op[a].n : nmax;
     // 8 wavefronts per workgroup share the moments of a long line; up to 1024
     // nodes smaller workgroups give more of them (1024^2 20.9 us against 22.9;
     // 1280^2 28.4 against 25.0)
-    if (nmax <= 1024) return terms == 3 ? run_far<4, 3>(L, s) : run_far<4, 6>(L, s);
-    return terms == 3 ? run_far<8, 3>(L, s) : run_far<8, 6>(L, s);
+    return nmax <= 1024 ? run_far<4>(L, s) : run_far<8>(L, s);
 }
 
 }  // namespace lbm

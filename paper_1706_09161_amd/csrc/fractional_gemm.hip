@@ -962,9 +962,7 @@ hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, cons
 namespace {
 
 // The axes that have their far-box operators go to that kernel, the others to
-// the dense kernels: one launch where all axes are of a kind.  Split BF16: up
-// to 1024 nodes only beyond 896 and where the dense register kernel lacks its
-// 16-wide steps (896 x 900: 17.2 us far, 17.6 dense; 1024^2 18.3, 16.5).
+// the dense kernels: one launch where all axes are of a kind.
 hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register_kernels, hipStream_t s)
 {
     auto dense = [&](FracLaunch& D) {
@@ -976,7 +974,7 @@ hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register
     memset(&D, 0, sizeof(D));
     for (int a = 0; a < L.naxes; ++a) {
         const int n = L.op[a].n;
-        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && (!bf16 || n > 1024 || (n > 896 && n % 16 != 0));
+        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && !bf16;
         FracLaunch& X = far ? F : D;
         X.op[X.naxes] = L.op[a];
         X.lay[X.naxes] = L.lay[a];
@@ -985,7 +983,7 @@ hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register
         ++X.naxes;
     }
     if (!F.naxes) return dense(L);
-    hipError_t e = launch_fractional_far(F, bf16 ? 3 : 6, s);
+    hipError_t e = launch_fractional_far(F, s);
     if (e == hipSuccess && D.naxes) e = dense(D);
     return e;
 }

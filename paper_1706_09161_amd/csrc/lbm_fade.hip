@@ -547,7 +547,7 @@ static size_t r256(size_t b) { return (b + 255) & ~(size_t)255; }
 // Image: per axis the generator, boundary columns, BF16 splits and pair words,
 // then the interpolation fragments (once), then every long axis' far-box
 // operators (filled on the device).  Only the first `upload` bytes are copied.
-size_t operator_image_bytes(const lbm_grid& grid, size_t* upload)
+size_t operator_image_bytes(const lbm_grid& grid, const lbm_params& P, size_t* upload)
 {
     size_t bytes = 0, tables = 0;
     bool far = false;
@@ -556,7 +556,7 @@ size_t operator_image_bytes(const lbm_grid& grid, size_t* upload)
         bytes += r256(sizeof(float) * (2 * n - 1)) + 2 * r256(sizeof(float) * n) +
                  2 * r256(sizeof(uint16_t) * (2 * n - 1)) + 2 * r256(sizeof(uint32_t) * pw_len_of((int)n));
         if (n <= kThirdPlaneMax) bytes += r256(sizeof(uint32_t) * pw_len_of((int)n));
-        if (far_used((int)n)) {
+        if (P.precision == LBM_FP32 && far_used((int)n)) {
             far = true;
             tables += r256(sizeof(uint16_t) * far_table_entries((int)n));
         }
@@ -597,7 +597,7 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         op.upper_only = P.p[mu] == 0.0;
         op.ends_excluded = 1;
         const bool third = n <= kThirdPlaneMax;
-        far = far || far_used(n);
+        far = far || (P.precision == LBM_FP32 && far_used(n));
         const size_t og = carve(sizeof(float) * (2 * n - 1));
         const size_t o0 = carve(sizeof(float) * n);
         const size_t oN = carve(sizeof(float) * n);
@@ -735,7 +735,7 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
 
     // operator data
     size_t upload = 0;
-    const size_t bytes = lbm::operator_image_bytes(*grid, &upload);
+    const size_t bytes = lbm::operator_image_bytes(*grid, *params, &upload);
     auto cleanup = [&]() { lbm_fade_destroy(h); };
     hipError_t e = hipMalloc(&h->opmem, bytes);
     if (e != hipSuccess) {

@@ -71,11 +71,11 @@ int fade_forward_step(lbm_fade* h, hipStream_t s);
 // Parameter checks of lbm_fade_create (error message set on failure).
 int validate_config(const lbm_grid* grid, int32_t lattice, const lbm_params* params);
 // Operator data of every axis (Toeplitz generator, boundary columns, BF16
-// splits and pair words, far-box operators): operator_image_bytes(grid) bytes
+// splits and pair words, far-box operators): operator_image_bytes() bytes
 // on the device, of which the first `upload` are a host image built in FP64;
 // launch_far_tables fills the rest once they are copied.  ops[mu] receives
 // the device pointers the data have at `base`.
-size_t operator_image_bytes(const lbm_grid& grid, size_t* upload);
+size_t operator_image_bytes(const lbm_grid& grid, const lbm_params& params, size_t* upload);
 void build_operator_image(const lbm_grid& grid, const lbm_params& params, unsigned char* host,
                           const unsigned char* base, AxisOp* ops);
 // Strided views of a node field for the operator along each axis.

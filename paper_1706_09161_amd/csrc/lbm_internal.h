@@ -143,14 +143,13 @@ hipError_t launch_fractional_bf16x3(FracLaunch& L, hipStream_t s);
 bool split_takes(const FracLaunch& L, int terms);
 hipError_t launch_fractional_split(FracLaunch& L, int terms, hipStream_t s);
 // Long axes (every operator needs its far_m table): near band plus moments of
-// far boxes; terms = 6 (FP32 products) or 3 (3-term split BF16 band).
-// far_used: axis lengths that take this path.  launch_far_tables fills far_m.
+// far boxes, LBM_FP32.  far_used: axis lengths that take this path.  launch_far_tables fills far_m.
 // far_reaches: the kernel's 32-bit byte offsets span the axis.
 bool far_used(int n);
 bool far_reaches(const AxisLayout& lay, int n);
 size_t far_table_entries(int n);
 void far_uv_fill(uint16_t* out, uint16_t (*to_bf16)(double), float (*to_float)(uint16_t));
 hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s);
-hipError_t launch_fractional_far(FracLaunch& L, int terms, hipStream_t s);
+hipError_t launch_fractional_far(FracLaunch& L, hipStream_t s);
 
 }  // namespace lbm

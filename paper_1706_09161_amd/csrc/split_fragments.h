@@ -158,20 +158,19 @@ struct Accumulators {
         else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(t, c, a, 0, 0, 0);
     }
     // one step of 16 k: x the C operand, y0 and y1 the Toeplitz operands of the two blocks
-    template <int TERMS>
-    __device__ __forceinline__ void products(const Frag3& x, const Frag3& y0, const Frag3& y1, int set)
+    __device__ __forceinline__ void add(const Frag3& x, const Frag3& y0, const Frag3& y1, int set)
     {
-        if constexpr (TERMS == 6) {
+        if constexpr (NT == 6) {
             corr[0] = mfma(x.l, y0.h, corr[0]);
             corr[1] = mfma(x.l, y1.h, corr[1]);
         }
         main_[set][0] = mfma(x.h, y0.h, main_[set][0]);
-        if constexpr (TERMS == 6) {
+        if constexpr (NT == 6) {
             corr[0] = mfma(x.h, y0.l, corr[0]);
             corr[1] = mfma(x.h, y1.l, corr[1]);
         }
         main_[set][1] = mfma(x.h, y1.h, main_[set][1]);
-        if constexpr (TERMS == 6) {
+        if constexpr (NT == 6) {
             corr[0] = mfma(x.m, y0.m, corr[0]);
             corr[1] = mfma(x.m, y1.m, corr[1]);
         }
@@ -179,14 +178,6 @@ struct Accumulators {
         corr[1] = mfma(x.m, y1.h, corr[1]);
         corr[0] = mfma(x.h, y0.m, corr[0]);
         corr[1] = mfma(x.h, y1.m, corr[1]);
-    }
-    __device__ __forceinline__ void add(const Frag3& x, const Frag3& y0, const Frag3& y1, int set)
-    {
-        products<NT>(x, y0, y1, set);
-    }
-    __device__ __forceinline__ void add6(const Frag3& x, const Frag3& y0, const Frag3& y1, int set)
-    {
-        products<6>(x, y0, y1, set);
     }
     // BOTH: set 1 of the main accumulators was used
     template <bool BOTH = true>
