@@ -424,7 +424,8 @@ struct AdjointState {
     int64_t nodes = 0;
     int K = 0;           // checkpoint interval the buffers were sized for
     int64_t nseg = 0;    // checkpoints allocated
-    float* ckpt = nullptr;
+    float* ckpt = nullptr;   // populations at the start of every segment
+    float* ckptC = nullptr;  // and C there, where the collision reads it (cc.moments)
     // recomputed segments, double-buffered (nbuf = 2) when both fit, so that
     // the next segment's recompute runs on a side stream during this
     // segment's reverse sweep
@@ -458,7 +459,7 @@ struct AdjointState {
 void adjoint_free(AdjointState* a)
 {
     if (!a) return;
-    void* ptrs[] = {a->ckpt, a->seg_f[0], a->seg_phi[0], a->seg_C[0], a->seg_f[1], a->seg_phi[1], a->seg_C[1],
+    void* ptrs[] = {a->ckpt, a->ckptC, a->seg_f[0], a->seg_phi[0], a->seg_C[0], a->seg_f[1], a->seg_phi[1], a->seg_C[1],
                     a->fbar, a->fdir, a->cbar, a->phibar, a->fdir2, a->cbar2, a->phibar2, a->Ckeep,
                     a->tu, a->tl, a->dS, a->part, a->part2, a->acc, a->opmem};
     for (void* p : ptrs) (void)hipFree(p);
@@ -574,16 +575,21 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
     const int64_t nodes = h->nodes;
     const int Q = h->Q, d = h->dim;
     const int64_t nseg = (n + K - 1) / K > 0 ? (n + K - 1) / K : 1;
-    if (A->ckpt && A->K == K && A->nseg >= nseg) return true;
-    void* old[] = {A->ckpt, A->seg_f[0], A->seg_phi[0], A->seg_C[0], A->seg_f[1], A->seg_phi[1], A->seg_C[1]};
+    if (A->ckpt && A->K == K && A->nseg >= nseg && (A->ckptC || !h->cc.moments)) return true;
+    void* old[] = {A->ckpt, A->ckptC, A->seg_f[0], A->seg_phi[0], A->seg_C[0], A->seg_f[1], A->seg_phi[1], A->seg_C[1]};
     for (void* p : old) (void)hipFree(p);
-    A->ckpt = nullptr;
+    A->ckpt = A->ckptC = nullptr;
     for (int b = 0; b < 2; ++b) A->seg_f[b] = A->seg_phi[b] = A->seg_C[b] = nullptr;
     A->nbuf = 0;
     A->K = K;
     A->nseg = nseg;
     const size_t fq = sizeof(float) * Q * nodes;
     if (hipMalloc(&A->ckpt, fq * nseg) != hipSuccess) return false;
+    if (h->cc.moments && hipMalloc(&A->ckptC, sizeof(float) * nodes * nseg) != hipSuccess) {
+        (void)hipFree(A->ckpt);
+        A->ckpt = A->ckptC = nullptr;
+        return false;
+    }
     for (int b = 0; b < 2; ++b) {
         const bool ok = hipMalloc(&A->seg_f[b], fq * (K + 1)) == hipSuccess &&
                         hipMalloc(&A->seg_phi[b], sizeof(float) * d * nodes * K) == hipSuccess &&
@@ -717,7 +723,11 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     };
     auto recompute = [&](int64_t sg, int b, hipStream_t st) -> int {
         const int len = seg_len(sg);
-        ADJ_TRY(launch_moment(h->cc, f_of(sg, b, 0), A->seg_C[b], st));
+        if (h->cc.moments)
+            ADJ_TRY(hipMemcpyAsync(A->seg_C[b], A->ckptC + sg * nodes, sizeof(float) * nodes,
+                                   hipMemcpyDeviceToDevice, st));
+        else
+            ADJ_TRY(launch_moment(h->cc, f_of(sg, b, 0), A->seg_C[b], st));
         for (int j = 0; j < len; ++j) {
             float* phi_j = A->seg_phi[b] + (int64_t)j * d * nodes;
             int rc = fade_run_phi(h, A->seg_C[b] + (int64_t)j * nodes, phi_j, st);
@@ -726,8 +736,8 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
                 return rc;
             }
             if (j + 1 < len)
-                ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, j), A->seg_f[b] + (int64_t)(j + 1) * Q * nodes,
-                                              phi_j, h->S, A->seg_C[b] + (int64_t)(j + 1) * nodes, st));
+                ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, j), A->seg_C[b] + (int64_t)j * nodes,
+                                              A->seg_f[b] + (int64_t)(j + 1) * Q * nodes, phi_j, h->S, A->seg_C[b] + (int64_t)(j + 1) * nodes, st));
         }
         return LBM_OK;
     };
@@ -740,12 +750,17 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     // --- forward pass with checkpoints (the handle's state advances to step n).
     // The last segment runs as its own recompute, into the buffer the reverse
     // sweep reads first, and its last step from there: the same kernels on the
-    // same inputs as the plain step (the moment kernel and the collide-stream
-    // kernel sum C in the same order), so the state is the same.
+    // same inputs as the plain step (C kept with the checkpoint, or summed by
+    // the moment kernel in the collide-stream kernel's order), so the state is
+    // the same.
     const int64_t t_last = (nseg - 1) * K;  // first step of the last segment
     for (int64_t t = 0; t < n; ++t) {
-        if (t % K == 0) ADJ_TRY(hipMemcpyAsync(A->ckpt + (t / K) * Q * nodes, h->f[h->cur], fq,
-                                               hipMemcpyDeviceToDevice, s));
+        if (t % K == 0) {
+            ADJ_TRY(hipMemcpyAsync(A->ckpt + (t / K) * Q * nodes, h->f[h->cur], fq, hipMemcpyDeviceToDevice, s));
+            if (h->cc.moments)
+                ADJ_TRY(hipMemcpyAsync(A->ckptC + (t / K) * nodes, h->C[h->cur], sizeof(float) * nodes,
+                                       hipMemcpyDeviceToDevice, s));
+        }
         if (t == t_last) break;
         int rc = fade_forward_step(h, s);
         if (rc) {
@@ -759,8 +774,9 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
         const int b = buf_of(sg), len = seg_len(sg);
         int rc = recompute(sg, b, s);
         if (rc) return rc;
-        ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, len - 1), h->f[1 - h->cur],
-                                      A->seg_phi[b] + (int64_t)(len - 1) * d * nodes, h->S, h->C, s));
+        ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, len - 1), A->seg_C[b] + (int64_t)(len - 1) * nodes,
+                                      h->f[1 - h->cur], A->seg_phi[b] + (int64_t)(len - 1) * d * nodes, h->S,
+                                      h->C[1 - h->cur], s));
         h->cur = 1 - h->cur;
         h->steps_done += len;
         h->at_initial_C = false;

@@ -4,8 +4,9 @@
 //
 // State between steps: populations f after streaming and the Dirichlet rule,
 // and their moment C = <1|f> (written by this kernel for the next step's
-// fractional term).  For every node x the kernel
-//   1. recomputes C(x) = sum_i f_i(x),
+// fractional term), or, where the collision allows it, C and the flux moments
+// alone (collision in moments, below).  For every node x the kernel
+//   1. takes C(x) = sum_i f_i(x),
 //   2. builds f^eq(C, Phi, u) (equations (Feq), (CoeffA_FADE3D)),
 //   3. collides: f* = f - R (f - f^eq) + w S dt with R = M^-1 Lambda M
 //      (equation (MRT-Coll); BGK: R = I / lambda, equation (LBE_FADE)),
@@ -24,8 +25,13 @@
 // f*_1 / f*_2 cross columns by lane shuffles; at the strip's two edges lanes
 // 0 and 63 also read the node just outside the strip and compute the one
 // population that crosses (one row of the collision operator).  Every node is
-// collided once (plus 2 halo rows per march), every population is read once
-// and written once: (2Q + d + 1) * 4 bytes per node from HBM (52 B for D2Q5).
+// collided once (plus 2 halo rows per march), the state is read once and
+// written once: (2Q + d + 1) * 4 bytes per node from HBM with populations (52 B
+// for D2Q5, 72 B for D3Q7), (2 + 3 d) * 4 with moments (32 B, 44 B).  HBM
+// bandwidth bounds both kernels where the state exceeds the Infinity Cache:
+// populations / moments 4096^2 180 / 98 us (4.8 / 5.5 TB/s), 256^3 260 / 149 us
+// (4.6 / 5.0 TB/s; a large copy reaches 5.0); in the cache 1024^2 11.7 / 7.1 us,
+// 128^3 32 / 17.5 us; below that the latency of a march, 64^2 4.4 / 3.9 us.
 //
 // 3D (D3Q7): a workgroup of NY wavefronts covers 64 x (NY - 2) nodes of one z
 // plane (one wave per y row, rows 0 and NY-1 halo, the x edges as in 2D) and
@@ -40,6 +46,7 @@
 // Offsets are 32-bit byte offsets from uniform base pointers (one VALU add per
 // address) while every array fits in 4 GiB, 64-bit otherwise.
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 #include <stdlib.h>
 
 #include <type_traits>
@@ -50,6 +57,7 @@ namespace lbm {
 namespace {
 
 constexpr int kStrip = 64;  // output columns per wavefront
+constexpr int kCUs = 256;   // of an MI355X
 
 // Tile index of workgroup b of nb.  Workgroups are dealt to the 8 XCDs round
 // robin (b mod 8); this gives each XCD one contiguous range of tiles instead,
@@ -219,15 +227,185 @@ __device__ inline void collide_x_pair(const CollideConsts& cc, const float (&f)[
 }
 
 // ---------------------------------------------------------------------------
+// Collision in moments.  With every free relaxation time equal to 1 the free
+// moments leave the collision at their equilibrium whatever they were, so it
+// depends on C and the flux moments j_a = f_{2a+1} - f_{2a+2} alone:
+//   f* = f^eq(C, Phi, u) + M^-1 (0, (Id - lambda-bar^-1)(j - j^eq), 0)
+//      : f*_{2a+1} = w Phi_a + g_a, f*_{2a+2} = w Phi_a - g_a,
+//        g_a = adv_a C + sum_b H_ab (j_b - 2 adv_b C), H = (Id - lambda-bar^-1) / 2,
+// plus w_i S dt, and f*_0 = C + S dt - (the sum of the others).
+// Streaming changes C by what enters less what leaves,
+//   C' = C + S dt + sum_i (f*_i(x - e_i) - f*_i(x)),  i >= 1,
+// small differences added to C once: f*_0, the largest population of the
+// opposite sign, does not enter, and neither do the roundings of a sum with
+// it.  They are alike from step to step where C changes slowly, and a C summed
+// from the populations drifts with them (2D, 64 x 64, 200 steps: 2.7e-6 of C
+// against 4.6e-7 so and 7.8e-7 with the operator R).
+// Between two steps of one run the state is then C and j (1 + d fields) in
+// place of the populations: a step reads 1 + 2 d values a node and writes
+// 1 + d, 8 instead of 13 in 2D and 11 instead of 18 in 3D.  From populations
+// these forms take f_1 .. and C, not f_0.  Errors against 64 bits (relative L2
+// of C, operator R / moments): 129 x 200 with a source, 1000 steps 8.6e-6 /
+// 4.2e-6, 256^2 100 steps 5.3e-6 / 5.0e-6, 45^3 60 steps 1.97e-6 / 1.94e-6.
+//
+// FORM of a kernel: how it collides and what its state is made of.  The three
+// moment forms and kMomentCollision round alike: j is the same difference of
+// the same values, whether stored or formed again.
+constexpr int kPopulations = 0;      // collision operator R, populations in and out
+constexpr int kMomentCollision = 1;  // collision in moments, populations and C in and out
+constexpr int kToMoments = 2;        // populations and C in, moments out
+constexpr int kMoments = 3;          // moments in and out
+constexpr int kFromMoments = 4;      // moments in, populations and C out
+template <int FORM>
+constexpr bool reads_moments = FORM >= kMoments;
+template <int FORM>
+constexpr bool writes_moments = FORM == kToMoments || FORM == kMoments;
+template <int Q, int FORM>
+constexpr int fields_in = reads_moments<FORM> ? (Q + 1) / 2 : Q;
+
+// C and j of a node from its input fields (C, then f_1 .. or j)
+template <int Q, int FORM>
+__device__ __forceinline__ void moments_of(const float (&v)[fields_in<Q, FORM>], float& C, float (&j)[(Q - 1) / 2])
+{
+    constexpr int d = (Q - 1) / 2;
+    C = v[0];
+#pragma unroll
+    for (int a = 0; a < d; ++a) {
+        if constexpr (reads_moments<FORM>) j[a] = v[1 + a];
+        else j[a] = v[2 * a + 1] - v[2 * a + 2];
+    }
+}
+
+// g_a of axis a (see above).  With VAR the node's H is the constant one less
+// half the node's dB (dB = 0 gives the constant path's bits).
+template <int Q, bool VAR>
+__device__ __forceinline__ float flux_part(const CollideConsts& cc, float C, const float (&j)[(Q - 1) / 2],
+                                           const float* db, int a)
+{
+#pragma clang fp contract(off)
+    constexpr int d = (Q - 1) / 2;
+    float h = 0.f;
+#pragma unroll
+    for (int b = 0; b < d; ++b) {
+        float H = cc.H[a * d + b];
+        if (VAR) H = fmaf(-0.5f, db[a <= b ? sym_index(d, a, b) : sym_index(d, b, a)], H);
+        h = fmaf(H, fmaf(-2.f * cc.adv[b], C, j[b]), h);
+    }
+    return fmaf(cc.adv[a], C, h);
+}
+
+// Collision of a node: its post-collision populations; in the moment forms
+// fs[0] is C + S dt instead of f*_0 (see stream).
+template <int Q, int FORM, bool VAR>
+__device__ __forceinline__ void collide(const CollideConsts& cc, const float (&v)[fields_in<Q, FORM>],
+                                        const float (&phi)[(Q - 1) / 2], float S, const float* db, float (&fs)[Q])
+{
+#pragma clang fp contract(off)
+    constexpr int d = (Q - 1) / 2;
+    if constexpr (FORM == kPopulations) {
+        collide_node<Q, VAR>(cc, v, phi, S, db, fs);
+    } else {
+        float C, j[d];
+        moments_of<Q, FORM>(v, C, j);
+#pragma unroll
+        for (int a = 0; a < d; ++a) {
+            const float e = cc.w[2 * a + 1] * phi[a];
+            const float g = flux_part<Q, VAR>(cc, C, j, db, a);
+            fs[2 * a + 1] = fmaf(cc.wSdt[2 * a + 1], S, e + g);
+            fs[2 * a + 2] = fmaf(cc.wSdt[2 * a + 2], S, e - g);
+        }
+        fs[0] = fmaf(cc.dt, S, C);
+    }
+}
+
+// Populations 1 and 2 only (a halo node at a strip edge)
+template <int Q, int FORM, bool VAR>
+__device__ __forceinline__ void collide_pair(const CollideConsts& cc, const float (&v)[fields_in<Q, FORM>],
+                                             const float (&phi)[(Q - 1) / 2], float S, const float* db, float& f1,
+                                             float& f2)
+{
+#pragma clang fp contract(off)
+    constexpr int d = (Q - 1) / 2;
+    if constexpr (FORM == kPopulations) {
+        collide_x_pair<Q, VAR>(cc, v, phi, S, db, f1, f2);
+    } else {
+        float C, j[d];
+        moments_of<Q, FORM>(v, C, j);
+        const float e = cc.w[1] * phi[0];
+        const float g = flux_part<Q, VAR>(cc, C, j, db, 0);
+        f1 = fmaf(cc.wSdt[1], S, e + g);
+        f2 = fmaf(cc.wSdt[2], S, e - g);
+    }
+}
+
+// Dirichlet rule, moment and store of one node: fs are its post-collision
+// populations (as collide leaves them), f[1..] what it pulled, unk the
+// populations that come from outside the box (nu of them), wall() its
+// Dirichlet value.  store(k, v) writes field k of the output state, store_C(c)
+// the moment beside the populations.
+template <int Q, int FORM, typename Wall, typename Store, typename StoreC>
+__device__ __forceinline__ void finish_node(const float (&fs)[Q], float (&f)[Q], const bool (&unk)[Q], bool stored,
+                                            Wall&& wall, Store&& store, StoreC&& store_C)
+{
+#pragma clang fp contract(off)
+    constexpr int d = (Q - 1) / 2;
+    int nu = 0;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) nu += unk[i];
+    float c;
+    if constexpr (FORM != kPopulations) {
+        float dc = 0.f;
+#pragma unroll
+        for (int a = 0; a < d; ++a) dc += (f[2 * a + 1] - fs[2 * a + 1]) + (f[2 * a + 2] - fs[2 * a + 2]);
+        c = fs[0] + dc;
+    }
+    if (FORM == kPopulations || !writes_moments<FORM> || nu > 0) {
+        f[0] = fs[0];
+        if constexpr (FORM != kPopulations) {
+            float s = 0.f;
+#pragma unroll
+            for (int a = 0; a < d; ++a) s += fs[2 * a + 1] + fs[2 * a + 2];
+            f[0] = fs[0] - s;
+        }
+    }
+    if (nu > 0) {
+        float known = f[0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i)
+            if (!unk[i]) known += f[i];
+        const float share = (wall() - known) * inv_count(nu);
+#pragma unroll
+        for (int i = 1; i < Q; ++i)
+            if (unk[i]) f[i] = share;
+    }
+    if (!stored) return;
+    if (FORM == kPopulations || nu > 0) {
+        c = f[0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) c += f[i];
+    }
+    if constexpr (writes_moments<FORM>) {
+        store(0, c);
+#pragma unroll
+        for (int a = 0; a < d; ++a) store(1 + a, f[2 * a + 1] - f[2 * a + 2]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) store(i, f[i]);
+        store_C(c);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // 2D D2Q5 fused kernel.  Rows move through a ring of D slots: while row y + 1
 // is collided, the loads of rows y + 2 .. y + D are in flight.
-template <bool HAS_S, bool VAR, bool NT, typename OFF>
+template <int FORM, bool HAS_S, bool VAR, bool NT, typename OFF>
 __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const float* __restrict__ fin,
-                                                         float* __restrict__ fout, const float* __restrict__ Phi,
+                                                         const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                          const float* __restrict__ S, float* __restrict__ Cout,
                                                          int rows_per_wave, int strips, int total_waves)
 {
     constexpr int D = 4;
+    constexpr int NI = fields_in<5, FORM>;
     const int nx = cc.n[0], ny = cc.n[1];
     const int64_t nodes = (int64_t)nx * ny;
     const int lane = threadIdx.x & 63;
@@ -241,17 +419,18 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
     const int y1 = min(ny, y0 + rows_per_wave);
 
     // uniform base pointers of every array
-    const float* fi[5];
+    const float* fi[NI];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) fi[i] = fin + i * nodes;
+    for (int i = 0; i < NI; ++i) fi[i] = fin + i * nodes;
+    if (FORM == kMomentCollision || FORM == kToMoments) fi[0] = Cin;
     const float* ph1 = Phi + nodes;
     const float* dbk[3];  // VAR: the three fields of dB (00, 01, 11)
 #pragma unroll
     for (int k = 0; k < 3; ++k) dbk[k] = VAR ? cc.dB + k * nodes : nullptr;
 
     struct Row {
-        float f[5], phi[2], s;  // this lane's node
-        float h[5], hphi[2], hs;  // the node just outside the strip (left half: x0 - 1, right half: x0 + 64)
+        float f[NI], phi[2], s;  // this lane's node
+        float h[NI], hphi[2], hs;  // the node just outside the strip (left half: x0 - 1, right half: x0 + 64)
         float db[3], hdb[2];      // VAR: dB of the node, row 0 of dB of the halo node
     };
     // Nodes outside the box read the nearest node inside it: every population
@@ -264,12 +443,12 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
         const int64_t rowoff = (int64_t)min(max(y, 0), ny - 1) * nx;
         const OFF b = (OFF)((rowoff + xc) * 4), bh = (OFF)((rowoff + hx) * 4);
 #pragma unroll
-        for (int i = 0; i < 5; ++i) r.f[i] = ldf(fi[i], b);
+        for (int i = 0; i < NI; ++i) r.f[i] = ldf(fi[i], b);
         r.phi[0] = ldf(Phi, b);
         r.phi[1] = ldf(ph1, b);
         r.s = HAS_S ? ldf(S, b) : 0.f;
 #pragma unroll
-        for (int i = 0; i < 5; ++i) r.h[i] = ldf(fi[i], bh);
+        for (int i = 0; i < NI; ++i) r.h[i] = ldf(fi[i], bh);
         r.hphi[0] = ldf(Phi, bh);
         r.hphi[1] = ldf(ph1, bh);
         r.hs = HAS_S ? ldf(S, bh) : 0.f;
@@ -283,9 +462,9 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
     // collision of a row: this lane's node, and the population its halo node
     // sends into the strip (f*_1 from the left neighbour, f*_2 from the right)
     auto collide_row = [&](const Row& r, float (&fs)[5], float& hv) {
-        collide_node<5, VAR>(cc, r.f, r.phi, r.s, r.db, fs);
+        collide<5, FORM, VAR>(cc, r.f, r.phi, r.s, r.db, fs);
         float h1, h2;
-        collide_x_pair<5, VAR>(cc, r.h, r.hphi, r.hs, r.hdb, h1, h2);
+        collide_pair<5, FORM, VAR>(cc, r.h, r.hphi, r.hs, r.hdb, h1, h2);
         hv = lane < 32 ? h1 : h2;
     };
 
@@ -312,35 +491,15 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
             const float sr = __shfl_down(cur[2], 1, 64);
             const float from_left = lane == 0 ? hcur : sl;
             const float from_right = lane == 63 ? hcur : sr;
-            float f[5] = {cur[0], from_left, from_right, prev3, nxt[4]};
+            float f[5] = {0.f, from_left, from_right, prev3, nxt[4]};
             const bool unk[5] = {false, x == 0, x == nx - 1, y == 0, y == ny - 1};
-            int nu = 0;
-            float known = 0.f;
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (unk[i]) ++nu;
-                else known += f[i];
-            }
-            if (nu > 0) {
+            const OFF b = (OFF)(((int64_t)y * nx + x) * 4);
+            finish_node<5, FORM>(
+                cur, f, unk, out_lane && y < y1,
                 // Dirichlet value of this wall node (clamped address: lanes past
                 // the grid and rows past the chunk are never stored)
-                const float cw =
-                    VAR ? ldf(cc.Cw, (OFF)(((int64_t)min(y, ny - 1) * nx + xc) * 4)) : cc.c_wall;
-                const float share = (cw - known) * inv_count(nu);
-#pragma unroll
-                for (int i = 0; i < 5; ++i)
-                    if (unk[i]) f[i] = share;
-            }
-            if (out_lane && y < y1) {
-                const OFF b = (OFF)(((int64_t)y * nx + x) * 4);
-                float c = 0.f;
-#pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    stv<NT>(fout + i * nodes, b, f[i]);
-                    c += f[i];
-                }
-                stv<NT>(Cout, b, c);
-            }
+                [&] { return VAR ? ldf(cc.Cw, (OFF)(((int64_t)min(y, ny - 1) * nx + xc) * 4)) : cc.c_wall; },
+                [&](int k, float v) { stv<NT>(fout + k * nodes, b, v); }, [&](float c) { stv<NT>(Cout, b, c); });
             prev3 = cur[3];
 #pragma unroll
             for (int i = 0; i < 5; ++i) cur[i] = nxt[i];
@@ -365,17 +524,18 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
 // planes (the loads of planes z + 2 .. z + D are in flight while plane z + 1
 // is collided).  f*_3 / f*_4 cross rows through LDS, double-buffered by plane
 // parity so one barrier per plane suffices.
-template <int NY, bool HAS_S, bool VAR, bool NT, typename OFF>
+template <int FORM, int NY, bool HAS_S, bool VAR, bool NT, typename OFF>
 __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, const float* __restrict__ fin,
-                                                             float* __restrict__ fout, const float* __restrict__ Phi,
+                                                             const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                              const float* __restrict__ S, float* __restrict__ Cout,
                                                              int planes_per_block, int strips_x, int strips_y)
 {
     // Two ring slots: the loads of plane z + 2 are in flight while plane z + 1
-    // is collided.  Fewer registers than a deeper ring (86 against 110 VGPRs)
-    // and faster on MI355X (256^3: 307 us against 313 with three slots, 339
-    // with four).
+    // is collided.  Fewer registers than a deeper ring (operator R: 86 against
+    // 110 VGPRs) and faster on MI355X (256^3: 307 us against 313 with three
+    // slots, 339 with four).
     constexpr int D = 2;
+    constexpr int NI = fields_in<7, FORM>;
     const int nx = cc.n[0], ny = cc.n[1], nz = cc.n[2];
     const int64_t plane = (int64_t)nx * ny;
     const int64_t nodes = plane * nz;
@@ -399,10 +559,11 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
     // one base per array and field offsets added per load (keeps the scalar
     // registers for the collision operator)
     const OFF fb = (OFF)(nodes * 4);  // bytes per field
+    const float* in0 = FORM == kMomentCollision || FORM == kToMoments ? Cin : fin;
 
     struct Plane {
-        float f[7], phi[3], s;
-        float h[7], hphi[3], hs;  // the node just outside the strip (left half: x0 - 1, right half: x0 + 64)
+        float f[NI], phi[3], s;
+        float h[NI], hphi[3], hs;  // the node just outside the strip (left half: x0 - 1, right half: x0 + 64)
         float db[6], hdb[3];      // VAR: dB of the node, row 0 of dB of the halo node
     };
     // nodes outside the box read the nearest node inside it (see the 2D kernel)
@@ -413,12 +574,12 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
         const int64_t zoff = (int64_t)min(max(z, 0), nz - 1) * plane;
         const OFF bm = (OFF)((zoff + xyc) * 4), bh = (OFF)((zoff + xyh) * 4);
 #pragma unroll
-        for (int i = 0; i < 7; ++i) p.f[i] = ldf(fin, bm + i * fb);
+        for (int i = 0; i < NI; ++i) p.f[i] = i == 0 ? ldf(in0, bm) : ldf(fin, bm + i * fb);
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) p.phi[mu] = ldf(Phi, bm + mu * fb);
         p.s = HAS_S ? ldf(S, bm) : 0.f;
 #pragma unroll
-        for (int i = 0; i < 7; ++i) p.h[i] = ldf(fin, bh + i * fb);
+        for (int i = 0; i < NI; ++i) p.h[i] = i == 0 ? ldf(in0, bh) : ldf(fin, bh + i * fb);
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) p.hphi[mu] = ldf(Phi, bh + mu * fb);
         p.hs = HAS_S ? ldf(S, bh) : 0.f;
@@ -430,9 +591,9 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
         }
     };
     auto collide_at = [&](const Plane& p, float (&fs)[7], float& hv) {
-        collide_node<7, VAR>(cc, p.f, p.phi, p.s, p.db, fs);
+        collide<7, FORM, VAR>(cc, p.f, p.phi, p.s, p.db, fs);
         float h1, h2;
-        collide_x_pair<7, VAR>(cc, p.h, p.hphi, p.hs, p.hdb, h1, h2);
+        collide_pair<7, FORM, VAR>(cc, p.h, p.hphi, p.hs, p.hdb, h1, h2);
         hv = lane < 32 ? h1 : h2;
     };
 
@@ -464,33 +625,13 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
             const float from_right = lane == 63 ? hcur : sr;
             const float from_below = row >= 1 ? sh3[par][row - 1][lane] : 0.f;       // f*_3 of y-1
             const float from_above = row + 1 < NY ? sh4[par][row + 1][lane] : 0.f;  // f*_4 of y+1
-            float f[7] = {cur[0], from_left, from_right, from_below, from_above, prev5, nxt[6]};
+            float f[7] = {0.f, from_left, from_right, from_below, from_above, prev5, nxt[6]};
             const bool unk[7] = {false, x == 0, x == nx - 1, y == 0, y == ny - 1, z == 0, z == nz - 1};
-            int nu = 0;
-            float known = 0.f;
-#pragma unroll
-            for (int i = 0; i < 7; ++i) {
-                if (unk[i]) ++nu;
-                else known += f[i];
-            }
-            if (nu > 0) {
-                const float cw =
-                    VAR ? ldf(cc.Cw, (OFF)(((int64_t)min(z, nz - 1) * plane + xyc) * 4)) : cc.c_wall;
-                const float share = (cw - known) * inv_count(nu);
-#pragma unroll
-                for (int i = 0; i < 7; ++i)
-                    if (unk[i]) f[i] = share;
-            }
-            if (out && z < z1) {
-                const OFF bo = (OFF)(((int64_t)z * plane + (int64_t)y * nx + x) * 4);
-                float c = 0.f;
-#pragma unroll
-                for (int i = 0; i < 7; ++i) {
-                    stv<NT>(fout, bo + i * fb, f[i]);
-                    c += f[i];
-                }
-                stv<NT>(Cout, bo, c);
-            }
+            const OFF bo = (OFF)(((int64_t)z * plane + (int64_t)y * nx + x) * 4);
+            finish_node<7, FORM>(
+                cur, f, unk, out && z < z1,
+                [&] { return VAR ? ldf(cc.Cw, (OFF)(((int64_t)min(z, nz - 1) * plane + xyc) * 4)) : cc.c_wall; },
+                [&](int k, float v) { stv<NT>(fout, bo + k * fb, v); }, [&](float c) { stv<NT>(Cout, bo, c); });
             prev5 = cur[5];
 #pragma unroll
             for (int i = 0; i < 7; ++i) cur[i] = nxt[i];
@@ -613,23 +754,44 @@ int collide_rows_override()
 
 }  // namespace
 
-hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, float* f_out, const float* Phi,
-                                 const float* S, float* C_out, hipStream_t s)
+bool moment_runs(const CollideConsts& cc) { return cc.moments && nodes_of(cc) * 7 * 4 < ((int64_t)1 << 32); }
+
+hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, const float* C_in, float* f_out,
+                                 const float* Phi, const float* S, float* C_out, hipStream_t s, StepState state)
 {
     // 32-bit byte offsets while every array (at most 7 fields of the node count) fits in 4 GiB
     const bool small = nodes_of(cc) * 7 * 4 < ((int64_t)1 << 32);
     // space-dependent diffusion tensor and wall values (both fields present)
     const bool var = cc.dB != nullptr;
     if (var && !cc.Cw) return hipErrorInvalidValue;
+    if (state != StepState::populations && !moment_runs(cc)) return hipErrorInvalidValue;
+    // C is read at neighbouring nodes too while it is written
+    if (state == StepState::populations && cc.moments && C_in == C_out) return hipErrorInvalidValue;
+    const bool in_m = state == StepState::moments || state == StepState::to_populations;
+    const bool out_m = state == StepState::moments || state == StepState::to_moments;
     // Non-temporal output stores once a step's traffic exceeds the 256 MB
     // Infinity Cache (below it, the next step reads the outputs from there).
     // Measured: 4096^2 177 -> 172 us, 256^3 303 -> 293 us; 1024^2 11.7 ->
     // 15.6 us if used there.  LBM_COLLIDE_NT = 0 / 1 forces it (tuning).
-    bool nt = nodes_of(cc) * (2 * cc.Q + cc.dim + 1) * 4 > ((int64_t)256 << 20);
+    const int fields = (in_m ? 1 + cc.dim : cc.Q) + (out_m ? 1 + cc.dim : cc.Q + 1) + cc.dim;
+    bool nt = nodes_of(cc) * fields * 4 > ((int64_t)256 << 20);
     if (const char* e = getenv("LBM_COLLIDE_NT")) {
         if (e[0] == '0') nt = false;
         if (e[0] == '1') nt = true;
     }
+    // kernel by state, source, space-dependent fields, stores and offsets
+    auto with_form = [&](auto&& f) {
+        with_flags(S != nullptr, var, nt, [&](auto hs, auto vr, auto ntc) {
+            switch (state) {
+            case StepState::to_moments: return f(std::integral_constant<int, kToMoments>{}, hs, vr, ntc);
+            case StepState::moments: return f(std::integral_constant<int, kMoments>{}, hs, vr, ntc);
+            case StepState::to_populations: return f(std::integral_constant<int, kFromMoments>{}, hs, vr, ntc);
+            case StepState::populations: break;
+            }
+            if (cc.moments) f(std::integral_constant<int, kMomentCollision>{}, hs, vr, ntc);
+            else f(std::integral_constant<int, kPopulations>{}, hs, vr, ntc);
+        });
+    };
     if (cc.dim == 2) {
         const int nx = cc.n[0], ny = cc.n[1];
         const int strips = (nx + kStrip - 1) / kStrip;
@@ -647,60 +809,77 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, flo
         const int waves = strips * chunks;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
         auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, cc, f_in, f_out, Phi, S, C_out, rows, strips,
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, rows, strips,
                                waves);
         };
-        with_flags(S != nullptr, var, nt, [&](auto hs, auto vr, auto ntc) {
+        with_form([&](auto form, auto hs, auto vr, auto ntc) {
             constexpr bool HS = decltype(hs)::value, VR = decltype(vr)::value, NT = decltype(ntc)::value;
-            if (small)
-                go(collide_stream_2d<HS, VR, NT, uint32_t>);
-            else
-                go(collide_stream_2d<HS, VR, NT, uint64_t>);
+            constexpr int F = decltype(form)::value;
+            if constexpr (F <= kMomentCollision) {
+                if (!small) return go(collide_stream_2d<F, HS, VR, NT, uint64_t>);
+            }
+            go(collide_stream_2d<F, HS, VR, NT, uint32_t>);
         });
         return hipGetLastError();
     }
     // Rows per workgroup (one wave per row, the first and last are halo):
     // NY = 10 (8 output rows, so 8 | ny tiles the usual sizes exactly) for the
-    // constant tensor: two workgroups fill a CU's 20 wave slots at 86 VGPRs,
-    // and the y-halo rows come from L2 lines the neighbouring workgroup on the
-    // same XCD fetched.  Measured at 256^3 (kernel trace; L2 fetches against
-    // the algorithmic reads): NY = 8 with 16-plane marches 308.2 us, 1.43x;
-    // NY = 10 with 16 planes 304.6 us, 1.16x; with 32 planes 290.7 us, 1.11x;
-    // NY = 12 or 16 were slower (one workgroup per CU).  The space-dependent
-    // variant (9 more values per ring plane, up to 256 VGPRs) keeps NY = 8.
-    auto launch3d = [&](auto ny_c, auto hs, auto vr, auto ntc) {
-        constexpr int NY = decltype(ny_c)::value;
+    // constant tensor; the y-halo rows come from L2 lines the neighbouring
+    // workgroup on the same XCD fetched.  Measured at 256^3 with the operator R
+    // (L2 fetches against the algorithmic reads): NY = 8 with 16-plane marches
+    // 308.2 us, 1.43x; NY = 10 with 16 planes 304.6 us, 1.16x; with 32 planes
+    // 290.7 us, 1.11x; NY = 12 or 16 were slower (one workgroup per CU).  The
+    // space-dependent variant (9 more values per ring plane) keeps NY = 8.
+    auto launch3d = [&](auto form, auto ny_c, auto hs, auto vr, auto ntc) {
+        constexpr int NY = decltype(ny_c)::value, F = decltype(form)::value;
         const int nx = cc.n[0], ny = cc.n[1], nz = cc.n[2];
         const int sx = (nx + kStrip - 1) / kStrip;
         const int sy = (ny + (NY - 2) - 1) / (NY - 2);
-        // Long z marches amortise the two halo planes; a queue of several
-        // workgroups per CU lets a new one start its ring while the others
-        // march.  Measured on MI355X with NY = 8 (8 / 16 / 32 / 64 planes):
-        // 128^3 33 / 38 / 39 / 69 us, 256^3 319 / 309 / 312 / 318, 384^3 1019 /
-        // 975 / 946 / 939: the longest march that still gives 2048 workgroups;
-        // with NY = 10 (256^3: 16 planes 304.6 us, 32 planes 290.7 us) the
-        // longest that gives 1024.
+        // Planes per march: the busiest CU collides k (planes + 2) planes when
+        // it gets k workgroups, and that product decides the time as long as
+        // the workgroups fill the CUs evenly.  Of the marches that give the CUs
+        // 1, 2, .. workgroups each, the one with the smallest product.  A lone
+        // workgroup per CU hides less latency, which counts while the state
+        // is read from the Infinity Cache.  Measured (collision in moments, us;
+        // in brackets workgroups, product): 256^3 16 planes 171 (2048, 144), 32
+        // 174 (1024, 136), 64 158 (512, 132), 128 151 (256, 130); 200 x 170 x
+        // 150 8 planes 47.7 (1672, 70), 30 44.1 (440, 64), 50 65.2 (264, 104);
+        // 128^3 8 planes 17.4 (512, 20), 16 18.5 (256, 18); 45^3 1 plane 5.9
+        // (270, 6), 2 4.7 (138, 4), 8 9.5 (36, 10).
         int planes = collide_rows_override();
         if (planes <= 0) {
-            const int64_t want = NY == 8 ? 2048 : 1024;
-            planes = 64;
-            while (planes > 8 && (int64_t)sx * sy * ((nz + planes - 1) / planes) < want) planes /= 2;
+            const int64_t per = (int64_t)sx * sy;
+            int64_t best = INT64_MAX;
+            const int64_t k0 = (per + kCUs - 1) / kCUs;
+            planes = nz;
+            for (int64_t k = k0; k < k0 + 16; ++k) {
+                const int64_t c = k * kCUs / per < nz ? k * kCUs / per : nz;
+                const int64_t p = (nz + c - 1) / c;
+                const int64_t cost = 4 * k * (p + 2) + (k == 1 && !nt ? p : 0);
+                if (cost < best) {
+                    best = cost;
+                    planes = (int)p;
+                }
+            }
         }
         const int chunks = (nz + planes - 1) / planes;
         const int64_t blocks = (int64_t)sx * sy * chunks;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
         constexpr bool HS = decltype(hs)::value, VR = decltype(vr)::value, NT = decltype(ntc)::value;
-        auto kern = small ? collide_stream_3d<NY, HS, VR, NT, uint32_t> : collide_stream_3d<NY, HS, VR, NT, uint64_t>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, cc, f_in, f_out, Phi, S, C_out, planes,
+        auto kern = collide_stream_3d<F, NY, HS, VR, NT, uint32_t>;
+        if constexpr (F <= kMomentCollision) {
+            if (!small) kern = collide_stream_3d<F, NY, HS, VR, NT, uint64_t>;
+        }
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, planes,
                            sx, sy);
         return hipSuccess;
     };
     hipError_t e = hipSuccess;
-    with_flags(S != nullptr, var, nt, [&](auto hs, auto vr, auto ntc) {
+    with_form([&](auto form, auto hs, auto vr, auto ntc) {
         if constexpr (decltype(vr)::value)
-            e = launch3d(std::integral_constant<int, 8>{}, hs, vr, ntc);
+            e = launch3d(form, std::integral_constant<int, 8>{}, hs, vr, ntc);
         else
-            e = launch3d(std::integral_constant<int, 10>{}, hs, vr, ntc);
+            e = launch3d(form, std::integral_constant<int, 10>{}, hs, vr, ntc);
     });
     if (e != hipSuccess) return e;
     return hipGetLastError();

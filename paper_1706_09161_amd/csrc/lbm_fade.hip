@@ -352,11 +352,47 @@ int run_phi(lbm_fade* h, const float* C, float* Phi, hipStream_t s)
 
 int forward_step(lbm_fade* h, hipStream_t s)
 {
-    int rc = run_phi(h, h->C, h->Phi, s);
+    int rc = run_phi(h, h->C[h->cur], h->Phi, s);
     if (rc) return rc;
-    HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->f[1 - h->cur], h->Phi, h->S, h->C, s));
+    HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi, h->S,
+                                       h->C[1 - h->cur], s));
     h->cur = 1 - h->cur;
     h->steps_done += 1;
+    h->at_initial_C = false;
+    return LBM_OK;
+}
+
+// n consecutive steps.  Where the collision is in moments the state between
+// two of them is C and the flux moments (in the population buffers), not the
+// populations: the first step reads populations, the last one writes them.
+// The results are those of n single steps, bit for bit.
+int run_steps(lbm_fade* h, int64_t n, hipStream_t s)
+{
+    // The first and the last step run kernels of their own, whose first launch
+    // costs about 1 us of instruction fetches each: two or three steps of a
+    // small grid (512 x 512: 4.4 us a step from and to moments, 4.9 from and to
+    // populations; 201 x 101 4.4 and 4.5) gain less than that.
+    if (n < 2 || (n < 4 && h->nodes < (1 << 18)) || !lbm::moment_runs(h->cc)) {
+        for (int64_t k = 0; k < n; ++k) {
+            const int rc = forward_step(h, s);
+            if (rc) return rc;
+        }
+        return LBM_OK;
+    }
+    const float* C = h->C[h->cur];
+    h->has_state = false;  // until the populations are back
+    for (int64_t k = 0; k < n; ++k) {
+        const int rc = run_phi(h, C, h->Phi, s);
+        if (rc) return rc;
+        const lbm::StepState st = k == 0 ? lbm::StepState::to_moments
+                                         : (k == n - 1 ? lbm::StepState::to_populations : lbm::StepState::moments);
+        HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi, h->S,
+                                           h->C[1 - h->cur], s, st));
+        h->cur = 1 - h->cur;
+        C = h->f[h->cur];  // field 0 of the moments
+    }
+    h->has_state = true;
+    h->steps_done += n;
     h->at_initial_C = false;
     return LBM_OK;
 }
@@ -398,11 +434,11 @@ int build_step_graph(lbm_fade* h)
     const int64_t done0 = h->steps_done;
     const bool init0 = h->at_initial_C;
     HIP_TRY(hipStreamBeginCapture(h->gstream, hipStreamCaptureModeRelaxed));
-    int rc = LBM_OK;
-    for (int k = 0; k < kGraphSteps && rc == LBM_OK; ++k) rc = forward_step(h, h->gstream);
+    const int rc = run_steps(h, kGraphSteps, h->gstream);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(h->gstream, &g);
-    h->cur = cur0;  // capturing ran nothing
+    h->has_state = true;  // capturing ran nothing
+    h->cur = cur0;
     h->steps_done = done0;
     h->at_initial_C = init0;
     if (rc != LBM_OK || e != hipSuccess) {
@@ -427,7 +463,7 @@ int build_step_graph(lbm_fade* h)
 // C := sum_i f_i of the current populations
 int refresh_C(lbm_fade* h, hipStream_t s)
 {
-    HIP_TRY(lbm::launch_moment(h->cc, h->f[h->cur], h->C, s));
+    HIP_TRY(lbm::launch_moment(h->cc, h->f[h->cur], h->C[h->cur], s));
     return LBM_OK;
 }
 
@@ -732,6 +768,12 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     cc.wSdt[0] = (float)(h->w0 * grid->dt);
     for (int i = 1; i < Q; ++i) cc.wSdt[i] = (float)(h->wi * grid->dt);
     cc.c_wall = (float)params->c_wall;
+    for (int a = 0; a < d; ++a)
+        for (int b = 0; b < d; ++b) cc.H[a * d + b] = (float)(0.5 * ((a == b ? 1.0 : 0.0) - h->lam_inv[a * d + b]));
+    h->free_times_one = params->collision == LBM_MRT;
+    for (int k = 0; k < Q - d - 1; ++k) h->free_times_one = h->free_times_one && params->tau_free[k] == 1.0;
+    cc.moments = h->free_times_one;
+    cc.dt = (float)grid->dt;
 
     // operator data
     size_t upload = 0;
@@ -761,12 +803,13 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     // state
     const size_t fbytes = sizeof(float) * Q * h->nodes;
     if (hipMalloc(&h->f[0], fbytes) != hipSuccess || hipMalloc(&h->f[1], fbytes) != hipSuccess ||
-        hipMalloc(&h->C, sizeof(float) * h->nodes) != hipSuccess ||
+        hipMalloc(&h->C[0], sizeof(float) * h->nodes * (h->free_times_one ? 2 : 1)) != hipSuccess ||
         hipMalloc(&h->Phi, sizeof(float) * d * h->nodes) != hipSuccess ||
         hipMalloc(&h->flag, sizeof(int) * 4) != hipSuccess) {
         cleanup();
         return fail(LBM_ENOMEM, "hipMalloc of the solver state failed");
     }
+    h->C[1] = h->C[0] + (h->free_times_one ? h->nodes : 0);
     *out = h;
     g_error.clear();
     return LBM_OK;
@@ -781,7 +824,7 @@ void lbm_fade_destroy(lbm_fade_t h)
     lbm::adjoint_free(h->adj);
     (void)hipFree(h->f[0]);
     (void)hipFree(h->f[1]);
-    (void)hipFree(h->C);
+    (void)hipFree(h->C[0]);
     (void)hipFree(h->Phi);
     (void)hipFree(h->S);
     (void)hipFree(h->dB);
@@ -797,11 +840,11 @@ int lbm_fade_set_C(lbm_fade_t h, const float* C0, int32_t on_device, void* strea
     int rc = check_device(h);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(h->C, C0, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
-    HIP_TRY(lbm::launch_wall_overwrite(h->cc, h->C, s));
-    rc = run_phi(h, h->C, h->Phi, s);
+    HIP_TRY(hipMemcpyAsync(h->C[h->cur], C0, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
+    HIP_TRY(lbm::launch_wall_overwrite(h->cc, h->C[h->cur], s));
+    rc = run_phi(h, h->C[h->cur], h->Phi, s);
     if (rc) return rc;
-    HIP_TRY(lbm::launch_equilibrium_init(h->cc, h->C, h->Phi, h->f[h->cur], s));
+    HIP_TRY(lbm::launch_equilibrium_init(h->cc, h->C[h->cur], h->Phi, h->f[h->cur], s));
     rc = refresh_C(h, s);
     if (rc) return rc;
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));  // the host buffer may be reused on return
@@ -899,6 +942,7 @@ int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on)
         drop_graph(h);
     }
     h->register_kernels = on != 0;
+    h->cc.moments = h->free_times_one && !h->register_kernels;
     return LBM_OK;
 }
 
@@ -931,13 +975,15 @@ int lbm_fade_step(lbm_fade_t h, int64_t n, void* stream)
             h->at_initial_C = false;
         }
     }
-    for (int64_t m = 0; m < n; ++m) {
-        rc = forward_step(h, s);
+    while (n > 0) {
+        const int64_t k = every > 0 ? (n < every - h->steps_done % every ? n : every - h->steps_done % every) : n;
+        rc = run_steps(h, k, s);
         if (rc) return rc;
+        n -= k;
         if (every > 0 && h->steps_done % every == 0) {
             int flag = 0;
             HIP_TRY(hipMemsetAsync(h->flag, 0, sizeof(int), s));
-            HIP_TRY(lbm::launch_nonfinite_check(h->C, h->nodes, h->flag, s));
+            HIP_TRY(lbm::launch_nonfinite_check(h->C[h->cur], h->nodes, h->flag, s));
             HIP_TRY(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
             if (flag) {
@@ -957,7 +1003,7 @@ int lbm_fade_get_C(lbm_fade_t h, float* dst, int32_t on_device, void* stream)
     int rc = check_device(h);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(dst, h->C, sizeof(float) * h->nodes, kind_from_dev(on_device), s));
+    HIP_TRY(hipMemcpyAsync(dst, h->C[h->cur], sizeof(float) * h->nodes, kind_from_dev(on_device), s));
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));
     return LBM_OK;
 }
@@ -1000,7 +1046,7 @@ int lbm_fade_apply_phi(lbm_fade_t h, const float* C, float* Phi, int32_t on_devi
         // the solver's own concentration
         if (!h->has_state) return fail(LBM_ESTATE, "no state yet");
         if (!on_device) return fail(LBM_EINVAL, "C = NULL needs a device Phi");
-        return run_phi(h, h->C, Phi, s);
+        return run_phi(h, h->C[h->cur], Phi, s);
     }
     if (on_device) return run_phi(h, C, Phi, s);
     float *dC = nullptr, *dP = nullptr;

@@ -102,6 +102,11 @@ struct CollideConsts {
     float R[kMaxQ * kMaxQ]; // M^-1 Lambda M (BGK: I / lambda), row-major
     float wSdt[kMaxQ];      // w_i dt (multiplies S)
     float c_wall;
+    // Collision in moments (every free relaxation time is 1): H = (Id -
+    // lambda-bar^-1) / 2, d x d row-major, and the time step.
+    int moments;
+    float H[9];
+    float dt;
     // Space-dependent coefficients (both null, or both set):
     //   dB: d(d+1)/2 node fields, the upper triangle (row by row) of
     //       lambda-bar(x)^-1 - lambda-bar^-1, added to the flux block of Lambda;
@@ -121,9 +126,16 @@ hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxe
 // outputs, in one launch.
 hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, const float* const* C, float* const* Phi,
                                  int nops, hipStream_t s);
-// C_out receives the new moment.
-hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, float* f_out, const float* Phi,
-                                 const float* S, float* C_out, hipStream_t s);
+// One step's collision, streaming and walls.  The state read and written is
+// the populations and C (C_in is read only where cc.moments, and must not be
+// C_out then), or, inside a run of steps where moment_runs(), the 1 + d fields
+// C, j_0, .. of the collision in moments (consecutive node fields in the same
+// buffers; C_in is not read then, C_out not written).
+enum class StepState { populations, to_moments, moments, to_populations };
+bool moment_runs(const CollideConsts& cc);
+hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, const float* C_in, float* f_out,
+                                 const float* Phi, const float* S, float* C_out, hipStream_t s,
+                                 StepState state = StepState::populations);
 hipError_t launch_equilibrium_init(const CollideConsts& cc, const float* C, const float* Phi, float* f,
                                    hipStream_t s);
 hipError_t launch_wall_overwrite(const CollideConsts& cc, float* C, hipStream_t s);
