@@ -845,8 +845,6 @@ int lbm_fade_set_C(lbm_fade_t h, const float* C0, int32_t on_device, void* strea
     rc = run_phi(h, h->C[h->cur], h->Phi, s);
     if (rc) return rc;
     HIP_TRY(lbm::launch_equilibrium_init(h->cc, h->C[h->cur], h->Phi, h->f[h->cur], s));
-    rc = refresh_C(h, s);
-    if (rc) return rc;
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));  // the host buffer may be reused on return
     h->has_state = true;
     h->at_initial_C = true;

@@ -136,8 +136,8 @@ bool moment_runs(const CollideConsts& cc);
 hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, const float* C_in, float* f_out,
                                  const float* Phi, const float* S, float* C_out, hipStream_t s,
                                  StepState state = StepState::populations);
-hipError_t launch_equilibrium_init(const CollideConsts& cc, const float* C, const float* Phi, float* f,
-                                   hipStream_t s);
+// f := f^eq(C, Phi), C := <1|f>
+hipError_t launch_equilibrium_init(const CollideConsts& cc, float* C, const float* Phi, float* f, hipStream_t s);
 hipError_t launch_wall_overwrite(const CollideConsts& cc, float* C, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t count, float v, hipStream_t s);
 hipError_t launch_moment(const CollideConsts& cc, const float* f, float* C, hipStream_t s);
