@@ -424,6 +424,8 @@ struct AdjointState {
     int64_t nodes = 0;
     int K = 0;           // checkpoint interval the buffers were sized for
     int64_t nseg = 0;    // checkpoints allocated
+    void* seg_mem[2] = {nullptr, nullptr};  // one allocation per segment buffer (the first also holds the checkpoints)
+    void* fields = nullptr;                 // one allocation: fbar .. acc below
     float* ckpt = nullptr;   // populations at the start of every segment
     float* ckptC = nullptr;  // and C there, where the collision reads it (cc.moments)
     // recomputed segments, double-buffered (nbuf = 2) when both fit, so that
@@ -459,9 +461,7 @@ struct AdjointState {
 void adjoint_free(AdjointState* a)
 {
     if (!a) return;
-    void* ptrs[] = {a->ckpt, a->ckptC, a->seg_f[0], a->seg_phi[0], a->seg_C[0], a->seg_f[1], a->seg_phi[1], a->seg_C[1],
-                    a->fbar, a->fdir, a->cbar, a->phibar, a->fdir2, a->cbar2, a->phibar2, a->Ckeep,
-                    a->tu, a->tl, a->dS, a->part, a->part2, a->acc, a->opmem};
+    void* ptrs[] = {a->seg_mem[0], a->seg_mem[1], a->fields, a->opmem};
     for (void* p : ptrs) (void)hipFree(p);
     hipEvent_t evs[] = {a->ev_fwd, a->ev_rec[0], a->ev_rec[1], a->ev_rev[0], a->ev_rev[1]};
     for (hipEvent_t e : evs)
@@ -576,33 +576,38 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
     const int Q = h->Q, d = h->dim;
     const int64_t nseg = (n + K - 1) / K > 0 ? (n + K - 1) / K : 1;
     if (A->ckpt && A->K == K && A->nseg >= nseg && (A->ckptC || !h->cc.moments)) return true;
-    void* old[] = {A->ckpt, A->ckptC, A->seg_f[0], A->seg_phi[0], A->seg_C[0], A->seg_f[1], A->seg_phi[1], A->seg_C[1]};
-    for (void* p : old) (void)hipFree(p);
+    for (int b = 0; b < 2; ++b) {
+        (void)hipFree(A->seg_mem[b]);
+        A->seg_mem[b] = nullptr;
+        A->seg_f[b] = A->seg_phi[b] = A->seg_C[b] = nullptr;
+    }
     A->ckpt = A->ckptC = nullptr;
-    for (int b = 0; b < 2; ++b) A->seg_f[b] = A->seg_phi[b] = A->seg_C[b] = nullptr;
     A->nbuf = 0;
     A->K = K;
     A->nseg = nseg;
-    const size_t fq = sizeof(float) * Q * nodes;
-    if (hipMalloc(&A->ckpt, fq * nseg) != hipSuccess) return false;
-    if (h->cc.moments && hipMalloc(&A->ckptC, sizeof(float) * nodes * nseg) != hipSuccess) {
-        (void)hipFree(A->ckpt);
-        A->ckpt = A->ckptC = nullptr;
-        return false;
-    }
+    const size_t field = sizeof(float) * nodes, fq = field * Q;
     for (int b = 0; b < 2; ++b) {
-        const bool ok = hipMalloc(&A->seg_f[b], fq * (K + 1)) == hipSuccess &&
-                        hipMalloc(&A->seg_phi[b], sizeof(float) * d * nodes * K) == hipSuccess &&
-                        hipMalloc(&A->seg_C[b], sizeof(float) * nodes * K) == hipSuccess;
-        if (!ok) {
+        Slab slab;
+        const size_t of = slab.take(fq * (K + 1)), op = slab.take(field * d * K), oC = slab.take(field * K);
+        size_t ock = 0, ockC = 0;
+        if (b == 0) {
+            ock = slab.take(fq * nseg);
+            if (h->cc.moments) ockC = slab.take(field * nseg);
+        }
+        if (hipMalloc(&A->seg_mem[b], slab.bytes) != hipSuccess) {
             // a second buffer is an optimisation: run single-buffered without it
             (void)hipGetLastError();
-            (void)hipFree(A->seg_f[b]);
-            (void)hipFree(A->seg_phi[b]);
-            (void)hipFree(A->seg_C[b]);
-            A->seg_f[b] = A->seg_phi[b] = A->seg_C[b] = nullptr;
+            A->seg_mem[b] = nullptr;
             if (b == 0) return false;
             break;
+        }
+        unsigned char* base = reinterpret_cast<unsigned char*>(A->seg_mem[b]);
+        A->seg_f[b] = reinterpret_cast<float*>(base + of);
+        A->seg_phi[b] = reinterpret_cast<float*>(base + op);
+        A->seg_C[b] = reinterpret_cast<float*>(base + oC);
+        if (b == 0) {
+            A->ckpt = reinterpret_cast<float*>(base + ock);
+            if (h->cc.moments) A->ckptC = reinterpret_cast<float*>(base + ockC);
         }
         A->nbuf = b + 1;
     }
@@ -612,21 +617,26 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
         for (hipEvent_t* e : evs)
             if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
     }
-    if (!A->fbar) {
+    if (!A->fields) {
         const int64_t nb = (nodes + kBlock - 1) / kBlock;
-        if (hipMalloc(&A->fbar, fq) != hipSuccess || hipMalloc(&A->fdir, fq) != hipSuccess ||
-            hipMalloc(&A->cbar, sizeof(float) * nodes) != hipSuccess ||
-            hipMalloc(&A->phibar, sizeof(float) * d * nodes) != hipSuccess ||
-            hipMalloc(&A->fdir2, fq) != hipSuccess || hipMalloc(&A->cbar2, sizeof(float) * nodes) != hipSuccess ||
-            hipMalloc(&A->phibar2, sizeof(float) * d * nodes) != hipSuccess ||
-            hipMalloc(&A->Ckeep, sizeof(float) * nodes) != hipSuccess ||
-            hipMalloc(&A->tu, sizeof(float) * d * nodes) != hipSuccess ||
-            hipMalloc(&A->tl, sizeof(float) * d * nodes) != hipSuccess ||
-            hipMalloc(&A->dS, sizeof(float) * nodes) != hipSuccess ||
-            hipMalloc(&A->part, sizeof(double) * nb_node_max(h) * (3 * 3 + 3 + 1 + 3)) != hipSuccess ||
-            hipMalloc(&A->part2, sizeof(double) * nb * 3) != hipSuccess ||
-            hipMalloc(&A->acc, sizeof(double) * 64) != hipSuccess)
+        float** const f32[] = {&A->fbar,    &A->fdir,  &A->fdir2, &A->phibar, &A->phibar2, &A->tu,
+                               &A->tl,      &A->cbar,  &A->cbar2, &A->Ckeep,  &A->dS};
+        const size_t f32_bytes[] = {fq,        fq,    fq,    field * d, field * d, field * d,
+                                    field * d, field, field, field,     field};
+        double** const f64[] = {&A->part, &A->part2, &A->acc};
+        const size_t f64_bytes[] = {sizeof(double) * nb_node_max(h) * (3 * 3 + 3 + 1 + 3), sizeof(double) * nb * 3,
+                                    sizeof(double) * 64};
+        Slab slab;
+        for (size_t b : f32_bytes) slab.take(b);
+        for (size_t b : f64_bytes) slab.take(b);
+        if (hipMalloc(&A->fields, slab.bytes) != hipSuccess) {
+            A->fields = nullptr;
             return false;
+        }
+        unsigned char* base = reinterpret_cast<unsigned char*>(A->fields);
+        slab = Slab();
+        for (int k = 0; k < 11; ++k) *f32[k] = reinterpret_cast<float*>(base + slab.take(f32_bytes[k]));
+        for (int k = 0; k < 3; ++k) *f64[k] = reinterpret_cast<double*>(base + slab.take(f64_bytes[k]));
     }
     return true;
 }

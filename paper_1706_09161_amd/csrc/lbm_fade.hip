@@ -775,18 +775,32 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     cc.moments = h->free_times_one;
     cc.dt = (float)grid->dt;
 
-    // operator data
+    // operator data and state, one allocation
     size_t upload = 0;
     const size_t bytes = lbm::operator_image_bytes(*grid, *params, &upload);
     auto cleanup = [&]() { lbm_fade_destroy(h); };
-    hipError_t e = hipMalloc(&h->opmem, bytes);
+    const size_t field = sizeof(float) * h->nodes;
+    lbm::Slab slab;
+    slab.take(bytes);
+    const size_t of0 = slab.take(field * Q), of1 = slab.take(field * Q);
+    const size_t oC = slab.take(field), oC1 = h->free_times_one ? slab.take(field) : oC;
+    const size_t oPhi = slab.take(field * d), oflag = slab.take(sizeof(int) * 4);
+    hipError_t e = hipMalloc(&h->mem, slab.bytes);
     if (e != hipSuccess) {
         cleanup();
-        return fail(LBM_ENOMEM, "hipMalloc of operator data failed");
+        return fail(LBM_ENOMEM, "hipMalloc of the operator data and the solver state failed");
     }
+    unsigned char* base = reinterpret_cast<unsigned char*>(h->mem);
+    auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
+    h->f[0] = at(of0);
+    h->f[1] = at(of1);
+    h->C[0] = at(oC);
+    h->C[1] = at(oC1);
+    h->Phi = at(oPhi);
+    h->flag = reinterpret_cast<int*>(base + oflag);
     std::vector<unsigned char> host(upload, 0);
-    lbm::build_operator_image(*grid, *params, host.data(), reinterpret_cast<const unsigned char*>(h->opmem), h->ops);
-    e = hipMemcpy(h->opmem, host.data(), upload, hipMemcpyHostToDevice);
+    lbm::build_operator_image(*grid, *params, host.data(), base, h->ops);
+    e = hipMemcpy(base, host.data(), upload, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         cleanup();
         return fail(LBM_EDEVICE, std::string("upload of operator data failed: ") + hipGetErrorString(e));
@@ -800,16 +814,6 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
         return fail(LBM_EDEVICE, std::string("far-box operators: ") + hipGetErrorString(e));
     }
     lbm::make_layouts(*grid, h->lays);
-    // state
-    const size_t fbytes = sizeof(float) * Q * h->nodes;
-    if (hipMalloc(&h->f[0], fbytes) != hipSuccess || hipMalloc(&h->f[1], fbytes) != hipSuccess ||
-        hipMalloc(&h->C[0], sizeof(float) * h->nodes * (h->free_times_one ? 2 : 1)) != hipSuccess ||
-        hipMalloc(&h->Phi, sizeof(float) * d * h->nodes) != hipSuccess ||
-        hipMalloc(&h->flag, sizeof(int) * 4) != hipSuccess) {
-        cleanup();
-        return fail(LBM_ENOMEM, "hipMalloc of the solver state failed");
-    }
-    h->C[1] = h->C[0] + (h->free_times_one ? h->nodes : 0);
     *out = h;
     g_error.clear();
     return LBM_OK;
@@ -822,15 +826,10 @@ void lbm_fade_destroy(lbm_fade_t h)
     drop_graph(h);
     if (h->gstream) (void)hipStreamDestroy(h->gstream);
     lbm::adjoint_free(h->adj);
-    (void)hipFree(h->f[0]);
-    (void)hipFree(h->f[1]);
-    (void)hipFree(h->C[0]);
-    (void)hipFree(h->Phi);
     (void)hipFree(h->S);
     (void)hipFree(h->dB);
     (void)hipFree(h->Cw);
-    (void)hipFree(h->opmem);
-    (void)hipFree(h->flag);
+    (void)hipFree(h->mem);
     delete h;
 }
 

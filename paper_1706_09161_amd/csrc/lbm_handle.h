@@ -19,9 +19,9 @@ struct lbm_fade {
     int device = 0;
     float* f[2] = {nullptr, nullptr};
     int cur = 0;  // f[cur] holds the current populations
-    // C[cur]: their moment.  Two fields of one allocation where the collision
-    // reads C (free_times_one: it writes C while neighbours still read it), one
-    // field otherwise (C[0] == C[1]).
+    // C[cur]: their moment.  Two fields where the collision reads C
+    // (free_times_one: it writes C while neighbours still read it), one field
+    // otherwise (C[0] == C[1]).
     float* C[2] = {nullptr, nullptr};
     float* Phi = nullptr;
     float* S = nullptr;
@@ -33,7 +33,7 @@ struct lbm_fade {
     bool var_wall = false;        // Cw set by lbm_fade_set_wall (else c_wall)
     bool register_kernels = false;  // dense axes on the register kernels (lbm_fade_set_register_kernels)
     bool free_times_one = false;    // MRT with every free relaxation time 1: collision in moments
-    void* opmem = nullptr;  // generators, corrections and BF16 splits of all axes
+    void* mem = nullptr;  // one allocation: the operator data of all axes, f, C, Phi and flag
     int* flag = nullptr;
     lbm::AxisOp ops[3];
     lbm::AxisLayout lays[3];
