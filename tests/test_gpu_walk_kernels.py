@@ -1,0 +1,39 @@
+"""The random walk's stable variable.
+
+A single step from the origin without drift is scale * S, so positions show
+the relative error of S itself.  S is evaluated from the same rounded
+arguments by the oracle (glibc: within 5.6 * 2^-53 of the exact value) and on
+the GPU (within 4.5 * 2^-53), and multiplied by the scale on both sides (half
+an ulp each): 16 * 2^-53 covers their difference. """
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _rw(dim, lo, hi, **kw):
+    from paper_1706_09161_amd.random_walk import RandomWalk
+
+    return RandomWalk(dim, lo, hi, **kw)
+
+
+@pytest.mark.parametrize("alpha,p", [(1.001, 0.0), (1.05, 0.5), (1.3, 1.0), (1.5, 0.37), (1.75, 0.9), (1.99, 0.0),
+                                     (1.999, 1.0), (2.0, 0.5)])
+def test_stable_variable(alpha, p):
+    n, big = 200000, 1e300
+    W = _rw(1, [-big], [big], alpha=[alpha], p=[p], D=[1.0], dt=0.1, seed=17)
+    P = oracle.rw_params(1, [-big], [big], [alpha], [p], [1.0], dt=0.1, seed=17)
+    x, alive = W.init_gaussian([0.0], 0.0, n)
+    assert float(x.abs().max()) == 0.0
+    W.walk(x, alive, 1)
+    xr, ar = oracle.rw_walk(P, np.zeros((1, n)), np.ones(n, np.uint8), 1)
+    got, ref = x.cpu().numpy()[0], xr[0]
+    assert np.array_equal(alive.cpu().numpy(), ar)
+    err = np.abs(got - ref) / np.abs(ref)
+    print(f"[gpu-walk] alpha={alpha} p={p}: max relative difference {err.max() * 2.0**53:.2f} * 2^-53", flush=True)
+    assert err.max() <= 16 * 2.0**-53
