@@ -156,14 +156,12 @@ __global__ __launch_bounds__(256) void rw_fill_u32(uint32_t* __restrict__ p, int
     if (i < count) p[i] = 0u;
 }
 
-__global__ __launch_bounds__(256) void rw_hist_kernel(RwConsts K, const double* __restrict__ x,
-                                                      const uint8_t* __restrict__ alive, int64_t n, int n0, int n1,
-                                                      int n2, double dx, uint32_t* __restrict__ counts)
+// Bin of particle k, or -1
+__device__ __forceinline__ int64_t bin_of(const RwConsts& K, const double* __restrict__ x, const uint8_t* __restrict__ alive,
+                                          int64_t n, int64_t k, const int (&nn)[3], double dx)
 {
 #pragma clang fp contract(off)
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n || !alive[k]) return;
-    const int nn[3] = {n0, n1, n2};
+    if (k >= n || !alive[k]) return -1;
     int64_t idx = 0, mul = 1;
     bool ok = true;
     for (int mu = 0; mu < K.dim; ++mu) {
@@ -172,7 +170,46 @@ __global__ __launch_bounds__(256) void rw_hist_kernel(RwConsts K, const double* 
         idx += (ok ? (int64_t)j : 0) * mul;
         mul *= nn[mu];
     }
-    if (ok) atomicAdd(&counts[idx], 1u);
+    return ok ? idx : -1;
+}
+
+__global__ __launch_bounds__(256) void rw_hist_kernel(RwConsts K, const double* __restrict__ x,
+                                                      const uint8_t* __restrict__ alive, int64_t n, int n0, int n1,
+                                                      int n2, double dx, uint32_t* __restrict__ counts)
+{
+    const int nn[3] = {n0, n1, n2};
+    const int64_t idx = bin_of(K, x, alive, n, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nn, dx);
+    if (idx >= 0) atomicAdd(&counts[idx], 1u);
+}
+
+// Many particles: they crowd into a few hundred cache lines of bins, and the
+// atomics on one line are carried out one after the other.  Each workgroup
+// counts `rounds` particles a thread in a direct-mapped table of bins in LDS
+// first (a bin whose slot another one holds goes to memory at once) and adds
+// each count it holds once.  1e6 particles, 201 x 201 bins: 106 us with an
+// atomic per particle, 37 us so; 2e5 36 and 28 (with launches), 1.3e5 25 and 25.
+constexpr int kSlots = 4096;
+__global__ __launch_bounds__(256) void rw_hist_many_kernel(RwConsts K, const double* __restrict__ x,
+                                                           const uint8_t* __restrict__ alive, int64_t n, int n0,
+                                                           int n1, int n2, double dx, uint32_t* __restrict__ counts,
+                                                           int rounds)
+{
+    __shared__ uint32_t held[kSlots], count[kSlots];  // bin + 1 of a slot (0: free), its particles
+    for (int i = threadIdx.x; i < kSlots; i += 256) held[i] = count[i] = 0u;
+    __syncthreads();
+    const int nn[3] = {n0, n1, n2};
+    const int64_t first = (int64_t)blockIdx.x * 256 * rounds + threadIdx.x;
+    for (int r = 0; r < rounds; ++r) {
+        const int64_t idx = bin_of(K, x, alive, n, first + (int64_t)r * 256, nn, dx);
+        if (idx < 0) continue;
+        const uint32_t key = (uint32_t)idx + 1u, slot = (uint32_t)idx & (kSlots - 1);
+        const uint32_t was = atomicCAS(&held[slot], 0u, key);
+        if (was == 0u || was == key) atomicAdd(&count[slot], 1u);
+        else atomicAdd(&counts[idx], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSlots; i += 256)
+        if (count[i]) atomicAdd(&counts[held[i] - 1u], count[i]);
 }
 
 int rw_fail(int code, const char* msg) { return lbm::set_error(code, msg); }
@@ -271,7 +308,12 @@ int lbm_rw_histogram(const lbm_rw_params* P, const double* x, const uint8_t* ali
     if (total > ((int64_t)1 << 34)) return rw_fail(LBM_EINVAL, "histogram too large");
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(rw_fill_u32, dim3(blocks_of(total)), dim3(256), 0, s, counts, total);
-    if (n > 0)
+    // a table per workgroup pays from two particles a thread on (keys are 32-bit)
+    const int64_t rounds = n / 65536 < 16 ? n / 65536 : 16;
+    if (rounds >= 2 && total < ((int64_t)1 << 32) - 1)
+        hipLaunchKernelGGL(rw_hist_many_kernel, dim3((unsigned)((n + 256 * rounds - 1) / (256 * rounds))), dim3(256),
+                           0, s, K, x, alive, n, nn[0], nn[1], nn[2], dx, counts, (int)rounds);
+    else if (n > 0)
         hipLaunchKernelGGL(rw_hist_kernel, dim3(blocks_of(n)), dim3(256), 0, s, K, x, alive, n, nn[0], nn[1], nn[2],
                            dx, counts);
     return hipGetLastError() == hipSuccess ? LBM_OK : rw_fail(LBM_EDEVICE, "launch of the histogram kernel failed");

@@ -1,10 +1,11 @@
-"""The random walk's stable variable.
+"""The random walk's stable variable and its histogram of many particles.
 
 A single step from the origin without drift is scale * S, so positions show
 the relative error of S itself.  S is evaluated from the same rounded
 arguments by the oracle (glibc: within 5.6 * 2^-53 of the exact value) and on
 the GPU (within 4.5 * 2^-53), and multiplied by the scale on both sides (half
-an ulp each): 16 * 2^-53 covers their difference. """
+an ulp each): 16 * 2^-53 covers their difference.  Counts are whole numbers
+and must be equal."""
 
 import numpy as np
 import pytest
@@ -37,3 +38,24 @@ def test_stable_variable(alpha, p):
     err = np.abs(got - ref) / np.abs(ref)
     print(f"[gpu-walk] alpha={alpha} p={p}: max relative difference {err.max() * 2.0**53:.2f} * 2^-53", flush=True)
     assert err.max() <= 16 * 2.0**-53
+
+
+@pytest.mark.parametrize("n", [131071, 131072, 131073, 200001, 1100000])
+@pytest.mark.parametrize("dim,nodes,width", [(1, [101], 0.3), (2, [201, 201], 0.02), (2, [2500, 1200], 0.3),
+                                             (3, [64, 33, 20], 0.1)])
+def test_histogram_of_many_particles(n, dim, nodes, width):
+    """Crowded and scattered particles, bins that share a table slot, dead and
+    outside particles, sizes beside the rule for the table."""
+    rng = np.random.default_rng(n + dim)
+    hi = [m - 1.0 for m in nodes]
+    x = np.stack([(0.5 + width * rng.standard_normal(n)) * h for h in hi])
+    alive = (rng.uniform(size=n) < 0.9).astype(np.uint8)
+    W = _rw(dim, [0.0] * dim, hi, alpha=[1.5] * dim, p=[0.5] * dim, D=[1.0] * dim)
+    got = W.histogram(torch.from_numpy(x).cuda(), torch.from_numpy(alive).cuda(), nodes, 1.0).cpu().numpy()
+    j = np.floor(x + 0.5)
+    ok = (alive == 1) & np.all([(j[mu] >= 0) & (j[mu] < nodes[mu]) for mu in range(dim)], axis=0)
+    idx = np.zeros(n, np.int64)
+    for mu in reversed(range(dim)):
+        idx = idx * nodes[mu] + j[mu].astype(np.int64)
+    ref = np.bincount(idx[ok], minlength=int(np.prod(nodes)))
+    assert np.array_equal(got.reshape(-1).astype(np.int64), ref)
