@@ -580,6 +580,25 @@ static const std::vector<uint16_t>& far_uv_table()
 // Every piece of the operator data sits at a 256-byte aligned offset.
 static size_t r256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// Whether axis mu takes the far-box kernel (LBM_FP32).  Beside axes that do not
+// it needs a launch of its own, 10 to 12 us that the dense sum of every axis in
+// one launch does not pay: worth it from 2^31 products on the long axes
+// (one-sided ones form half of theirs).  Measured, two launches / one, us:
+// 801 x 650 32.5 / 18.7, 1024 x 300 25.1 / 12.8, 1500 x 750 43 / 38, 2000 x 300
+// 32 / 29, but 3000 x 300 39 / 46, 2000 x 700 45 / 52, 1024 x 64 x 64 54 / 71.
+static bool far_axis(const lbm_grid& grid, const lbm_params& P, int mu)
+{
+    if (P.precision != LBM_FP32 || !far_used(grid.n[mu])) return false;
+    double nodes = 1.0, products = 0.0;
+    bool all = true;
+    for (int a = 0; a < grid.dim; ++a) nodes *= grid.n[a];
+    for (int a = 0; a < grid.dim; ++a) {
+        if (far_used(grid.n[a])) products += nodes * grid.n[a] * (P.p[a] == 0.0 || P.p[a] == 1.0 ? 0.5 : 1.0);
+        else all = false;
+    }
+    return all || products >= 0x1p31;
+}
+
 // Image: per axis the generator, boundary columns, BF16 splits and pair words,
 // then the interpolation fragments (once), then every long axis' far-box
 // operators (filled on the device).  Only the first `upload` bytes are copied.
@@ -592,7 +611,7 @@ size_t operator_image_bytes(const lbm_grid& grid, const lbm_params& P, size_t* u
         bytes += r256(sizeof(float) * (2 * n - 1)) + 2 * r256(sizeof(float) * n) +
                  2 * r256(sizeof(uint16_t) * (2 * n - 1)) + 2 * r256(sizeof(uint32_t) * pw_len_of((int)n));
         if (n <= kThirdPlaneMax) bytes += r256(sizeof(uint32_t) * pw_len_of((int)n));
-        if (P.precision == LBM_FP32 && far_used((int)n)) {
+        if (far_axis(grid, P, mu)) {
             far = true;
             tables += r256(sizeof(uint16_t) * far_table_entries((int)n));
         }
@@ -633,7 +652,7 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
         op.upper_only = P.p[mu] == 0.0;
         op.ends_excluded = 1;
         const bool third = n <= kThirdPlaneMax;
-        far = far || (P.precision == LBM_FP32 && far_used(n));
+        far = far || far_axis(grid, P, mu);
         const size_t og = carve(sizeof(float) * (2 * n - 1));
         const size_t o0 = carve(sizeof(float) * n);
         const size_t oN = carve(sizeof(float) * n);
@@ -685,7 +704,7 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
     const std::vector<uint16_t>& uv = far_uv_table();
     memcpy(host + ou, uv.data(), sizeof(uint16_t) * uv.size());
     for (int mu = 0; mu < grid.dim; ++mu) {
-        if (!far_used(grid.n[mu])) continue;
+        if (!far_axis(grid, P, mu)) continue;
         ops[mu].far_m = reinterpret_cast<const uint16_t*>(base + carve(sizeof(uint16_t) * far_table_entries(grid.n[mu])));
         ops[mu].far_uv = reinterpret_cast<const uint16_t*>(base + ou);
     }

@@ -1,8 +1,8 @@
 """The fractional term of long axes (near band plus moments of far boxes) at
 the sizes where it can go wrong: the longest dense axes and the shortest and
 longest ones beyond, ends of boxes, ragged ends, few lines, every axis of a
-grid, a long axis beside a short one, one- and two-sided operators; and lines
-that hold infinities or NaN.
+grid, a long axis beside a short one (summed densely with it, or on its own),
+one- and two-sided operators; and lines that hold infinities or NaN.
 
 FP32 tolerance, relative to sum_k |K_jk| |C_k| (the value itself: C and every
 weight are >= 0): an accumulator of the band is rounded 8 times and the three
@@ -39,6 +39,13 @@ CASES = [
     (3, [9, 855, 4], [1.5, 1.3, 1.5], [0.5, 0.3, 0.5]),
     (3, [5, 7, 1100], [1.5, 1.5, 1.8], [0.5, 0.5, 0.9]),
     (3, [866, 5, 4], [2.0, 1.5, 1.5], [0.5, 0.5, 0.5]),
+    # every axis long, or enough lines beside a short axis for a launch of the long one's own
+    (2, [1153, 770], [1.5, 1.6], [0.5, 1.0]),
+    (2, [4096, 769], [1.2, 1.5], [0.7, 0.0]),
+    (2, [771, 4095], [1.5, 1.4], [0.5, 0.0]),
+    (3, [866, 64, 45], [2.0, 1.5, 1.5], [0.5, 0.5, 0.5]),
+    (3, [24, 1100, 90], [1.5, 1.3, 1.5], [0.5, 0.3, 0.5]),
+    (3, [70, 30, 1100], [1.5, 1.5, 1.8], [0.5, 0.5, 0.9]),
 ]
 
 
@@ -80,12 +87,13 @@ def test_lines_with_infinities_and_nan(size, axis, p):
     """One line with +inf, one with -inf, one with NaN at an inner node, on
     dense axes and one with boxes: the outputs whose integral reaches the node take its value
     (every weight is > 0) and every other output is that of the finite field."""
-    n, at = [size, 40], size // 2 - 17
+    lines = 800 if size == 900 else 40  # boxes: every axis long
+    n, at = [size, lines], size // 2 - 17
     pa = list(p)
     if axis == 1:
         n, pa = n[::-1], pa[::-1]
     cfg = synth.small(2, n, alpha=[1.4, 1.4], p=pa, seed=52)
-    C = np.random.default_rng(24).uniform(0.5, 1.0, (40, size)).astype(np.float32)  # [line, node]
+    C = np.random.default_rng(24).uniform(0.5, 1.0, (lines, size)).astype(np.float32)  # [line, node]
     bad = C.copy()
     for line, v in ((3, np.inf), (17, -np.inf), (38, np.nan)):
         bad[line, at] = v
@@ -100,7 +108,7 @@ def test_lines_with_infinities_and_nan(size, axis, p):
         good, got = good.T, got.T
     j = np.arange(size)
     reach = np.ones(size, bool) if 0 < p[0] < 1 else (j >= at if p[0] == 1.0 else j <= at)
-    for line in range(40):
+    for line in range(lines):
         want = good[line].copy()
         if line in (3, 17, 38):
             want[reach] = bad[line, at]
