@@ -72,11 +72,17 @@ def gemm_bytes_per_step(cfg: dict) -> float:
 
 
 def collide_bytes_per_step(cfg: dict) -> float:
-    """Algorithmic HBM bytes of the fused collide-stream kernel: Q populations
-    read and written, d fractional terms read, C written (FP32)."""
+    """Algorithmic HBM bytes of the fused collide-stream kernel, average over
+    the 10 steps of a replayed graph.  The state between its steps is C and d
+    flux moments where every free relaxation time is 1 (the first step reads
+    Q populations, C among them as a field of its own; the last one writes Q
+    populations and C), else the populations; d fractional terms are read."""
     d = cfg["dim"]
     Q = 2 * d + 1
-    return (2 * Q + d + 1) * 4.0 * float(np.prod(cfg["n"][:d]))
+    per_node = 2 * Q + d + 1
+    if cfg.get("collision", "MRT") == "MRT" and all(t == 1.0 for t in cfg.get("tau_free", [1.0])):
+        per_node = (8 * (2 * (1 + d) + d) + (Q + 1 + d + d) + (1 + d + Q + 1 + d)) / 10
+    return per_node * 4.0 * float(np.prod(cfg["n"][:d]))
 
 
 def reference_file(name: str, steps: int):

@@ -160,9 +160,10 @@ LBM_API int lbm_fade_set_wall(lbm_fade_t h, const float* Cw, int32_t on_device, 
  * register kernels (FP32 MFMA, or BF16 MFMA for LBM_BF16X3) whatever the grid,
  * and the collision applies M^-1 Lambda M to the populations; 0 (the default):
  * the fastest kernel for the grid, and a collision in moments where every free
- * relaxation time is 1.  The results differ in rounding only.  For callers whose results must not change in the last bits
- * when the choice of kernels does (the autograd wrapper uses it: its gradients
- * are FP64 values).  May synchronise the device. */
+ * relaxation time is 1.  The results differ in rounding only.  For callers whose
+ * results must not change in the last bits when the choice of kernels does (the
+ * autograd wrapper uses it: its gradients are FP64 values).  May synchronise the
+ * device. */
 LBM_API int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on);
 
 /* Advance n >= 0 time steps.  Asynchronous; the launches of one step are: the
