@@ -24,7 +24,7 @@
 //
 // Instruction issue bounds the walk: about 330 vector instructions a draw, 70
 // of them Philox, where the library's log, sin, cos and pow took 950.  1e6
-// particles, 50 steps, 2D: 2.17 -> 0.86 ms; 4e6 particles, 100 steps: 99e9
+// particles, 50 steps, 2D: 2.17 -> 0.84 ms; 4e6 particles, 100 steps: 110e9
 // draws a second.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -129,13 +129,18 @@ __global__ __launch_bounds__(256) void rw_walk_kernel(RwConsts K, double* __rest
     bool live = true;
     for (uint32_t i = 0; i < nsteps; ++i) {
         const uint32_t s = step0 + 1 + i;
-#pragma unroll
+        // one copy of the draw: the axes take turns in p[0] (unrolled, the
+        // constants of every axis and polynomial spill scalar registers)
+#pragma unroll 1
         for (int mu = 0; mu < DIM; ++mu) {
             double u1, u2;
             draw2(K, first + k, s, kPurposeStep + (uint32_t)mu, u1, u2);
             const double S = lbm::stable_math::stable(table, K.alpha[mu], K.inv_alpha[mu], K.expo[mu], K.B[mu], K.Sc[mu],
                                                       u1, u2);
-            p[mu] += K.udt[mu] + K.scale[mu] * S;
+            const double moved = p[0] + (K.udt[mu] + K.scale[mu] * S);
+#pragma unroll
+            for (int nu = 0; nu + 1 < DIM; ++nu) p[nu] = p[nu + 1];
+            p[DIM - 1] = moved;
         }
         bool in = true;
 #pragma unroll
