@@ -156,9 +156,8 @@ LBM_API int lbm_fade_set_diffusion(lbm_fade_t h, const float* D, int32_t on_devi
  * runs.  NULL goes back to c_wall.  Host input synchronises `stream`. */
 LBM_API int lbm_fade_set_wall(lbm_fade_t h, const float* Cw, int32_t on_device, void* stream);
 
-/* on != 0: the fractional term of axes of at most 768 nodes runs on the
- * register kernels (FP32 MFMA, or BF16 MFMA for LBM_BF16X3) whatever the grid,
- * and the collision applies M^-1 Lambda M to the populations; 0 (the default):
+/* on != 0: the fractional term of every axis runs on the register kernels
+ * (FP32 MFMA, or BF16 MFMA for LBM_BF16X3) whatever the grid, and the collision applies M^-1 Lambda M to the populations; 0 (the default):
  * the fastest kernel for the grid, and a collision in moments where every free
  * relaxation time is 1.  The results differ in rounding only.  For callers whose
  * results must not change in the last bits when the choice of kernels does (the

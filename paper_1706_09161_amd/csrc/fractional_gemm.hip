@@ -974,7 +974,7 @@ hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register
     memset(&D, 0, sizeof(D));
     for (int a = 0; a < L.naxes; ++a) {
         const int n = L.op[a].n;
-        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && !bf16;
+        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && !register_kernels && !bf16;
         FracLaunch& X = far ? F : D;
         X.op[X.naxes] = L.op[a];
         X.lay[X.naxes] = L.lay[a];

@@ -117,8 +117,8 @@ struct CollideConsts {
 
 // Kernel launchers (host functions).  All return a hipError_t.
 // Fractional term of all axes: axis a reads C + a * in_stride (in_stride = 0:
-// one field for every axis) and writes Phi + a * nodes.  register_kernels: the
-// axes without boxes stay on the register kernels.
+// one field for every axis) and writes Phi + a * nodes.  register_kernels: every
+// axis on the register kernels.
 hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision,
                              bool register_kernels, const float* C, int64_t in_stride, float* Phi, int64_t nodes,
                              hipStream_t s);

@@ -192,8 +192,9 @@ class LbmFade:
         L.check(L.lib().lbm_fade_set_wall(self._h, ptr, dev, _stream_ptr(stream)))
 
     def set_register_kernels(self, on: bool):
-        """Keep axes of at most 768 nodes on the register kernels of the
-        fractional term (results then do not depend on the kernel selection)."""
+        """Keep every axis on the register kernels of the fractional term, and the
+        collision on the populations (results then do not depend on which
+        faster kernels a grid would take)."""
         L.check(L.lib().lbm_fade_set_register_kernels(self._h, int(bool(on))))
 
     def step(self, n: int = 1, stream=None):
