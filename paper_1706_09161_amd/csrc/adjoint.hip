@@ -548,8 +548,7 @@ bool build_ops(lbm_fade* h, AdjointState* A)
         U.gen = reinterpret_cast<const float*>(base + oU);
         U.col0 = U.colN = zeros;
         U.gen_hi = U.gen_lo = nullptr;
-        U.pw_hi = U.pw_lo = U.pw_l3 = nullptr;
-        U.far_m = U.far_uv = nullptr;
+        U.pw_hi = U.pw_lo = nullptr;
         AxisOp& L = A->opsL[mu];
         L = U;
         L.lower_only = 1;

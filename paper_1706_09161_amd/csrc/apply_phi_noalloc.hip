@@ -90,7 +90,7 @@ extern "C" int lbm_fade_apply_phi_noalloc(const lbm_grid* grid, const lbm_params
     rc = scratch_of(dev, &base);
     if (rc) return rc;
 
-    lbm::AxisOp ops[3];
+    lbm::AxisData ops[3];
     lbm::AxisLayout lays[3];
     std::vector<unsigned char> host(upload, 0);
     lbm::build_operator_image(*grid, *params, host.data(), base, ops);

@@ -79,7 +79,7 @@ __device__ __forceinline__ void six16(const Frag3& a, const Frag3& b, f32x4& mai
 }
 
 template <bool CONTIG, int NW>
-__device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay, const float* __restrict__ C,
+__device__ __forceinline__ void far_tile(const SplitOp& op, const AxisLayout& lay, const float* __restrict__ C,
                                          float* __restrict__ Phi, int tiles_l, int splits, int bid, int total,
                                          unsigned char* smem)
 {
@@ -369,7 +369,7 @@ __device__ __forceinline__ void far_tile(const AxisOp& op, const AxisLayout& lay
 }
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW, 2) void fractional_far(FracLaunch L)
+__global__ __launch_bounds__(64 * NW, 2) void fractional_far(SplitLaunch L)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_f[];
     const int bid = blockIdx.x;
@@ -446,10 +446,10 @@ size_t far_lds(int n)
 }
 
 template <int NW>
-hipError_t run_far(FracLaunch& L, hipStream_t s)
+hipError_t run_far(SplitLaunch& L, hipStream_t s)
 {
     size_t lds = 0;
-    int64_t per[kMaxOps];
+    int64_t per[3];
     for (int a = 0; a < L.naxes; ++a) {
         const AxisLayout& lay = L.lay[a];
         L.tiles_m[a] = (int)((lay.lines + 31) / 32);
@@ -531,12 +531,12 @@ void far_uv_fill(uint16_t* out, uint16_t (*to_bf16)(double), float (*to_float)(u
                 put(6144 + (size_t)ks * 3 * 64 * 8, lane, e, tab[(32 * ks + 8 * (lane / 16) + e) * kRank + lane % 16]);
 }
 
-hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s)
+hipError_t launch_far_tables(const AxisData* ops, int nops, hipStream_t s)
 {
     FarTables F = {};
     int k = 0, blocks = 0;
     for (int a = 0; a < nops; ++a) {
-        const AxisOp& op = ops[a];
+        const AxisData& op = ops[a];
         if (!op.far_m) continue;
         F.first[k] = blocks;
         F.nsp[k] = far_sources(op.n);
@@ -553,7 +553,7 @@ hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fractional_far(FracLaunch& L, hipStream_t s)
+hipError_t launch_fractional_far(SplitLaunch& L, hipStream_t s)
 {
     int nmax = 0;
     for (int a = 0; a < L.naxes; ++a) nmax = L.op[a].n > nmax ? L.op[a].n : nmax;

@@ -909,11 +909,31 @@ hipError_t run_f32_ring(FracLaunch& L, hipStream_t s)
 }  // namespace
 
 namespace {
+
 hipError_t run_f32_auto(FracLaunch& L, hipStream_t s);
-hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register_kernels, hipStream_t s);
+
+// A launch of the register kernels for `count` of the axes, axis[k].
+hipError_t run_register(const AxisData* ops, const AxisLayout* lays, const int* axis, int count, bool bf16,
+                        const float* C, int64_t in_stride, float* Phi, int64_t nodes, hipStream_t s)
+{
+    FracLaunch L;
+    memset(&L, 0, sizeof(L));
+    L.naxes = count;
+    for (int k = 0; k < count; ++k) {
+        const int a = axis[k];
+        L.op[k] = ops[a];
+        L.lay[k] = lays[a];
+        L.C[k] = C + a * in_stride;
+        L.Phi[k] = Phi + a * nodes;
+    }
+    return bf16 ? launch_fractional_bf16x3(L, s) : run_f32_auto(L, s);
 }
 
-hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision,
+}  // namespace
+
+// The axes that have their far-box operators go to that kernel, the others to
+// the dense kernels: one launch where all axes are of a kind.
+hipError_t launch_fractional(const AxisData* ops, const AxisLayout* lays, int naxes, int precision,
                              bool register_kernels, const float* C, int64_t in_stride, float* Phi, int64_t nodes,
                              hipStream_t s)
 {
@@ -930,17 +950,38 @@ hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxe
         }
         return hipSuccess;
     }
-    FracLaunch L;
-    memset(&L, 0, sizeof(L));
-    L.naxes = naxes;
+    const bool bf16 = precision == 1;
+    const int every[3] = {0, 1, 2};
+    if (register_kernels || tile_choice(bf16 ? "LBM_BF16_TILE" : "LBM_FP32_TILE") != 0)
+        return run_register(ops, lays, every, naxes, bf16, C, in_stride, Phi, nodes, s);
+    auto split_launch = [&](const int* axis, int count) {
+        SplitLaunch L = {};
+        L.naxes = count;
+        for (int k = 0; k < count; ++k) {
+            const int a = axis[k];
+            const AxisData& o = ops[a];
+            L.op[k] = {o.n,     o.lower_only, o.upper_only, o.ends_excluded, o.gen,    o.col0,  o.colN,
+                       o.pw_hi, o.pw_lo,      o.pw_l3,      o.far_m,         o.far_uv, o.pw_top};
+            L.lay[k] = lays[a];
+            L.C[k] = C + a * in_stride;
+            L.Phi[k] = Phi + a * nodes;
+        }
+        return L;
+    };
+    int far[3], dense[3], nfar = 0, ndense = 0;
     for (int a = 0; a < naxes; ++a) {
-        L.op[a] = ops[a];
-        L.lay[a] = lays[a];
-        L.C[a] = C + a * in_stride;
-        L.Phi[a] = Phi + a * nodes;
+        if (!bf16 && ops[a].far_m && far_reaches(lays[a], ops[a].n)) far[nfar++] = a;
+        else dense[ndense++] = a;
     }
-    const bool forced = tile_choice(precision == 1 ? "LBM_BF16_TILE" : "LBM_FP32_TILE") != 0;
-    return launch_by_length(L, precision == 1, forced, register_kernels, s);
+    if (nfar) {
+        SplitLaunch F = split_launch(far, nfar);
+        const hipError_t e = launch_fractional_far(F, s);
+        if (e != hipSuccess || !ndense) return e;
+    }
+    SplitLaunch D = split_launch(dense, ndense);
+    const int terms = bf16 ? 3 : 6;
+    if (split_takes(D, terms)) return launch_fractional_split(D, terms, s);
+    return run_register(ops, lays, dense, ndense, bf16, C, in_stride, Phi, nodes, s);
 }
 
 hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, const float* const* C, float* const* Phi,
@@ -956,37 +997,10 @@ hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, cons
         L.C[a] = C[a];
         L.Phi[a] = Phi[a];
     }
-    return launch_by_length(L, false, tile_choice("LBM_FP32_TILE") != 0, true, s);
+    return run_f32_auto(L, s);
 }
 
 namespace {
-
-// The axes that have their far-box operators go to that kernel, the others to
-// the dense kernels: one launch where all axes are of a kind.
-hipError_t launch_by_length(FracLaunch& L, bool bf16, bool forced, bool register_kernels, hipStream_t s)
-{
-    auto dense = [&](FracLaunch& D) {
-        if (!forced && !register_kernels && split_takes(D, bf16 ? 3 : 6)) return launch_fractional_split(D, bf16 ? 3 : 6, s);
-        return bf16 ? launch_fractional_bf16x3(D, s) : run_f32_auto(D, s);
-    };
-    FracLaunch F, D;
-    memset(&F, 0, sizeof(F));
-    memset(&D, 0, sizeof(D));
-    for (int a = 0; a < L.naxes; ++a) {
-        const int n = L.op[a].n;
-        const bool far = L.op[a].far_m && far_reaches(L.lay[a], n) && !forced && !register_kernels && !bf16;
-        FracLaunch& X = far ? F : D;
-        X.op[X.naxes] = L.op[a];
-        X.lay[X.naxes] = L.lay[a];
-        X.C[X.naxes] = L.C[a];
-        X.Phi[X.naxes] = L.Phi[a];
-        ++X.naxes;
-    }
-    if (!F.naxes) return dense(L);
-    hipError_t e = launch_fractional_far(F, s);
-    if (e == hipSuccess && D.naxes) e = dense(D);
-    return e;
-}
 
 hipError_t run_f32_auto(FracLaunch& L, hipStream_t s)
 {

@@ -46,7 +46,7 @@ constexpr int kJW = 64;  // outputs per wavefront
 
 // KC: k per chunk.  A staged line takes KC + 8 BF16 (16 lines hit distinct banks).
 template <bool CONTIG, int WJ, int KC, int NT>
-__device__ __forceinline__ void split_tile(const AxisOp& op, const AxisLayout& lay, const float* __restrict__ C,
+__device__ __forceinline__ void split_tile(const SplitOp& op, const AxisLayout& lay, const float* __restrict__ C,
                                            float* __restrict__ Phi, int tiles_l, int tiles_j, int bid, int total,
                                            unsigned char* smem)
 {
@@ -266,7 +266,7 @@ __device__ __forceinline__ void split_tile(const AxisOp& op, const AxisLayout& l
 }
 
 template <int WJ, int KC, int NT>
-__global__ __launch_bounds__(kThreads, WJ == 1 && KC == 64 ? 4 : 2) void fractional_split(FracLaunch L)
+__global__ __launch_bounds__(kThreads, WJ == 1 && KC == 64 ? 4 : 2) void fractional_split(SplitLaunch L)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_s[];
     const int bid = blockIdx.x;
@@ -284,12 +284,12 @@ __global__ __launch_bounds__(kThreads, WJ == 1 && KC == 64 ? 4 : 2) void fractio
 
 // tiles_m = line blocks of 32, tiles_n = output tiles
 template <int WJ, int KC, int NT>
-void split_grid(FracLaunch& L, int64_t& grid, size_t& lds)
+void split_grid(SplitLaunch& L, int64_t& grid, size_t& lds)
 {
     grid = 0;
     lds = 0;
     for (int a = 0; a < L.naxes; ++a) {
-        const AxisOp& op = L.op[a];
+        const SplitOp& op = L.op[a];
         const AxisLayout& lay = L.lay[a];
         L.tiles_m[a] = (int)((lay.lines + 31) / 32);
         L.tiles_n[a] = (op.n + kJW * WJ - 1) / (kJW * WJ);
@@ -306,7 +306,7 @@ void split_grid(FracLaunch& L, int64_t& grid, size_t& lds)
 }
 
 template <int WJ, int KC, int NT>
-hipError_t run_split(FracLaunch& L, hipStream_t s)
+hipError_t run_split(SplitLaunch& L, hipStream_t s)
 {
     int64_t grid = 0;
     size_t lds = 0;
@@ -332,11 +332,11 @@ hipError_t run_split(FracLaunch& L, hipStream_t s)
 // (two output tiles at 128 nodes: 128^3 19.3 against 22.0; four beyond:
 // 256^3 141 against 201 with one, 171 with two).
 template <int NT>
-hipError_t pick(FracLaunch& L, hipStream_t s)
+hipError_t pick(SplitLaunch& L, hipStream_t s)
 {
     int nmax = 0;
     for (int a = 0; a < L.naxes; ++a) nmax = L.op[a].n > nmax ? L.op[a].n : nmax;
-    FracLaunch T = L;
+    SplitLaunch T = L;
     int64_t grid = 0;
     size_t lds = 0;
     if (nmax <= 64) return run_split<1, 64, NT>(L, s);
@@ -357,7 +357,7 @@ hipError_t pick(FracLaunch& L, hipStream_t s)
 // and 65 to 128 nodes (128^2 5.65 against 5.37), split BF16 with every axis a
 // multiple of 16 beyond 832 nodes (1024^2 18.0 against 16.5; 768^2 12.9
 // against 14.8).
-bool split_takes(const FracLaunch& L, int terms)
+bool split_takes(const SplitLaunch& L, int terms)
 {
     int nmax = 0, align = 0;
     bool batched = L.naxes > 2;
@@ -372,7 +372,7 @@ bool split_takes(const FracLaunch& L, int terms)
     return align % 16 != 0 || nmax <= 832;
 }
 
-hipError_t launch_fractional_split(FracLaunch& L, int terms, hipStream_t s)
+hipError_t launch_fractional_split(SplitLaunch& L, int terms, hipStream_t s)
 {
     return terms == 3 ? pick<3>(L, s) : pick<6>(L, s);
 }

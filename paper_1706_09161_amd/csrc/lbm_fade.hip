@@ -632,7 +632,7 @@ static void fill_pair_words(const uint16_t* gen, int n, uint32_t* pw)
 }
 
 void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned char* host, const unsigned char* base,
-                          AxisOp* ops)
+                          AxisData* ops)
 {
     size_t off = 0;
     auto carve = [&](size_t nbytes) {
@@ -644,7 +644,7 @@ void build_operator_image(const lbm_grid& grid, const lbm_params& P, unsigned ch
     for (int mu = 0; mu < grid.dim; ++mu) {
         const int n = grid.n[mu];
         const AxisWeights W = make_axis_weights(n, 2.0 - P.alpha[mu], P.p[mu], P.g[mu], grid.dx, P.flux_form);
-        AxisOp& op = ops[mu];
+        AxisData& op = ops[mu];
         op.n = n;
         op.lower_only = P.p[mu] == 1.0;
         op.upper_only = P.p[mu] == 0.0;

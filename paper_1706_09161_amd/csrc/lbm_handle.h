@@ -32,7 +32,7 @@ struct lbm_fade {
     bool free_times_one = false;    // MRT with every free relaxation time 1: collision in moments
     void* mem = nullptr;  // one allocation: the operator data of all axes, f, C, Phi and flag
     int* flag = nullptr;
-    lbm::AxisOp ops[3];
+    lbm::AxisData ops[3];
     lbm::AxisLayout lays[3];
     lbm::CollideConsts cc;
     bool has_state = false;
@@ -78,7 +78,7 @@ int validate_config(const lbm_grid* grid, int32_t lattice, const lbm_params* par
 // the device pointers the data have at `base`.
 size_t operator_image_bytes(const lbm_grid& grid, const lbm_params& params, size_t* upload);
 void build_operator_image(const lbm_grid& grid, const lbm_params& params, unsigned char* host,
-                          const unsigned char* base, AxisOp* ops);
+                          const unsigned char* base, AxisData* ops);
 // Strided views of a node field for the operator along each axis.
 void make_layouts(const lbm_grid& grid, AxisLayout* lays);
 // Adjoint driver (adjoint.hip).

@@ -33,10 +33,16 @@ struct AxisOp {
     // for x in [0, pw_top + n + 288).  pw_top = 16 ceil((n + 512) / 16) - 1.
     const uint32_t* pw_hi;
     const uint32_t* pw_lo;
-    // The third plane of T = hi + lo + l3 (same indexing), for the FP32 products
-    // formed from exact three-term splits; null on axes beyond kThirdPlaneMax.
-    const uint32_t* pw_l3;
     int pw_top;
+};
+
+// Everything the library holds of one axis' operator (host side; a kernel gets
+// the part it reads, AxisOp or SplitOp, by value).
+struct AxisData : AxisOp {
+    // The third plane of T = hi + lo + l3 (indexed as the other two), for the
+    // FP32 products formed from exact three-term splits; null on axes beyond
+    // kThirdPlaneMax.
+    const uint32_t* pw_l3;
     // Far part of a long axis (fractional_far.hip; null where it is not used):
     // operators between boxes, and the interpolation fragments.  T(d) at a
     // distance |d| >= 64 is far_pos a(d) for d > 0, far_neg a(-d) for d < 0,
@@ -93,6 +99,25 @@ struct FracLaunch {
     int lgroup;  // one-sided operators: line tiles per group of the tile order (0 = all of an XCD's)
 };
 
+// The same for the kernels on three-term splits (fractional_split.hip,
+// fractional_far.hip): the axes of one step, and of an operator what they read.
+struct SplitOp {
+    int n, lower_only, upper_only, ends_excluded;
+    const float *gen, *col0, *colN;
+    const uint32_t *pw_hi, *pw_lo, *pw_l3;
+    const uint16_t *far_m, *far_uv;
+    int pw_top;
+};
+struct SplitLaunch {
+    SplitOp op[3];
+    AxisLayout lay[3];
+    int tiles_m[3], tiles_n[3];
+    int first[4];
+    const float* C[3];
+    float* Phi[3];
+    int naxes;
+};
+
 // Constants of the fused collide-stream kernel (Sec. 2.2-2.5).
 struct CollideConsts {
     int dim, Q;
@@ -119,11 +144,11 @@ struct CollideConsts {
 // Fractional term of all axes: axis a reads C + a * in_stride (in_stride = 0:
 // one field for every axis) and writes Phi + a * nodes.  register_kernels: every
 // axis on the register kernels.
-hipError_t launch_fractional(const AxisOp* ops, const AxisLayout* lays, int naxes, int precision,
+hipError_t launch_fractional(const AxisData* ops, const AxisLayout* lays, int naxes, int precision,
                              bool register_kernels, const float* C, int64_t in_stride, float* Phi, int64_t nodes,
                              hipStream_t s);
 // FP32 only: nops (<= kMaxOps) operators with their own layouts, inputs and
-// outputs, in one launch.
+// outputs, in one launch of a register kernel.
 hipError_t launch_fractional_ops(const AxisOp* ops, const AxisLayout* lays, const float* const* C, float* const* Phi,
                                  int nops, hipStream_t s);
 // Places of several buffers in one allocation.  An allocation and its release
@@ -162,10 +187,10 @@ int64_t big_tiles(const FracLaunch& L);
 // Tile configuration forced through an environment variable (0 = automatic).
 int tile_choice(const char* var);
 hipError_t launch_fractional_bf16x3(FracLaunch& L, hipStream_t s);
-// Dense kernel on the BF16 matrix cores; terms as below.  split_takes: the
-// launches it is used for.
-bool split_takes(const FracLaunch& L, int terms);
-hipError_t launch_fractional_split(FracLaunch& L, int terms, hipStream_t s);
+// Dense kernel on the BF16 matrix cores; terms: BF16 products per FP32 product
+// (6), or of LBM_BF16X3 (3).  split_takes: the launches it is used for.
+bool split_takes(const SplitLaunch& L, int terms);
+hipError_t launch_fractional_split(SplitLaunch& L, int terms, hipStream_t s);
 // Long axes (every operator needs its far_m table): near band plus moments of
 // far boxes, LBM_FP32.  far_used: axis lengths that take this path.  launch_far_tables fills far_m.
 // far_reaches: the kernel's 32-bit byte offsets span the axis.
@@ -173,7 +198,7 @@ bool far_used(int n);
 bool far_reaches(const AxisLayout& lay, int n);
 size_t far_table_entries(int n);
 void far_uv_fill(uint16_t* out, uint16_t (*to_bf16)(double), float (*to_float)(uint16_t));
-hipError_t launch_far_tables(const AxisOp* ops, int nops, hipStream_t s);
-hipError_t launch_fractional_far(FracLaunch& L, hipStream_t s);
+hipError_t launch_far_tables(const AxisData* ops, int nops, hipStream_t s);
+hipError_t launch_fractional_far(SplitLaunch& L, hipStream_t s);
 
 }  // namespace lbm

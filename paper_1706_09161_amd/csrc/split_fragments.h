@@ -221,7 +221,7 @@ struct Boundary {
 // outputs jw .. n - 1.  ls4, ks4: byte strides of lines and nodes.  REDO:
 // values whose sum is not finite are formed again from the definition.
 template <bool CONTIG, bool REDO>
-__device__ __forceinline__ void store_tile(const AxisOp& op, const f32x16 (&sum)[2], int u_lo, int u_hi,
+__device__ __forceinline__ void store_tile(const SplitOp& op, const f32x16 (&sum)[2], int u_lo, int u_hi,
                                            const Boundary& bd, const float* Cb, float* Pb, int nl, int jw, int k_lo,
                                            int k_hi, uint32_t ls4, uint32_t ks4)
 {
