@@ -980,7 +980,7 @@ hipError_t launch_fractional(const AxisData* ops, const AxisLayout* lays, int na
     }
     SplitLaunch D = split_launch(dense, ndense);
     const int terms = bf16 ? 3 : 6;
-    if (split_takes(D, terms)) return launch_fractional_split(D, terms, s);
+    if (split_takes(D, naxes, terms)) return launch_fractional_split(D, terms, s);
     return run_register(ops, lays, dense, ndense, bf16, C, in_stride, Phi, nodes, s);
 }
 

@@ -32,6 +32,7 @@
 // matrix work is 61 us and the bytes (C per axis, Phi) 80 us at 5 TB/s; small
 // grids are a chain of loads, split, products and stores.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 
 #include "split_fragments.h"
 
@@ -352,24 +353,42 @@ hipError_t pick(SplitLaunch& L, hipStream_t s)
 }  // namespace
 
 // Whether this kernel takes a launch: axes with their third plane and within
-// 32-bit byte offsets, except where the register kernels are still faster
-// (us, this kernel against them): FP32 in 2D with every axis a multiple of 8
-// and 65 to 128 nodes (128^2 5.65 against 5.37), split BF16 with every axis a
-// multiple of 16 beyond 832 nodes (1024^2 18.0 against 16.5; 768^2 12.9
-// against 14.8).
-bool split_takes(const SplitLaunch& L, int terms)
+// 32-bit byte offsets, except in 2D where the register kernels are still faster
+// (us, this kernel / the register kernel):
+//  * FP32, every axis a multiple of 8: 65 to 128 nodes (72^2 5.44 / 5.17, 128^2
+//    5.45 / 5.32), and strided axes beyond 128 up to 224 nodes on the longer
+//    axis (136^2 6.55 / 6.31, 208^2 6.52 / 6.37, 96 x 192 6.44 / 6.24), or 384 if
+//    an operator is two-sided (240^2 6.57 / 6.51, 304^2 7.77 / 7.69, 160 x 240
+//    6.58 / 6.44).  The next ones are this kernel's: one-sided 240^2 6.53 / 6.74,
+//    480^2 8.97 / 9.11, and a strided axis of up to 128 beside a longer
+//    contiguous one, 200 x 128 5.89 / 6.33, 400 x 320 7.85 / 8.44.
+//  * Split BF16, every axis a multiple of 16: both of 385 to 512 nodes with a
+//    two-sided operator (400^2 7.82 / 7.61, 512^2 7.81 / 7.69; one-sided 512^2
+//    7.71 / 7.82, 384^2 6.95 / 7.53, 528^2 9.32 / 9.95), and beyond 832 (896^2
+//    15.98 / 14.99, 1024^2 18.41 / 15.24; 832^2 13.55 / 14.61).
+// In 3D the line blocks are many enough to hide this kernel's set-up (split
+// BF16 1024 x 64 x 64 42.1 / 54.3, 2048 x 64 x 64 93 / 114) until one axis is
+// nearly all of the grid (4096 x 16 x 16 53.6 / 45.4).
+bool split_takes(const SplitLaunch& L, int dim, int terms)
 {
-    int nmax = 0, align = 0;
-    bool batched = L.naxes > 2;
+    int nmax = 0, nmin = INT_MAX, align = 0, ny = 0;  // ny: longest strided axis
+    bool two_sided = false;
     for (int a = 0; a < L.naxes; ++a) {
-        const int n = L.op[a].n;
-        if (!L.op[a].pw_l3 || !far_reaches(L.lay[a], n)) return false;
-        nmax = n > nmax ? n : nmax;
-        align |= n;
-        batched = batched || L.lay[a].batches > 1;
+        const SplitOp& op = L.op[a];
+        if (!op.pw_l3 || !far_reaches(L.lay[a], op.n)) return false;
+        nmax = op.n > nmax ? op.n : nmax;
+        nmin = op.n < nmin ? op.n : nmin;
+        align |= op.n;
+        if (!L.lay[a].contiguous && op.n > ny) ny = op.n;
+        two_sided = two_sided || (!op.lower_only && !op.upper_only);
     }
-    if (terms == 6) return batched || align % 8 != 0 || nmax <= 64 || nmax > 128;
-    return align % 16 != 0 || nmax <= 832;
+    if (terms == 6) {
+        if (dim == 3 || align % 8 != 0 || nmax <= 64) return true;
+        return nmax > 128 && (ny <= 128 || nmax > (two_sided ? 384 : 224));
+    }
+    if (align % 16 != 0) return true;
+    if (dim == 3) return nmax <= 2048;
+    return nmax <= 832 && !(two_sided && nmin > 384 && nmax <= 512);
 }
 
 hipError_t launch_fractional_split(SplitLaunch& L, int terms, hipStream_t s)

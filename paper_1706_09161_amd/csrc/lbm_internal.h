@@ -189,7 +189,7 @@ int tile_choice(const char* var);
 hipError_t launch_fractional_bf16x3(FracLaunch& L, hipStream_t s);
 // Dense kernel on the BF16 matrix cores; terms: BF16 products per FP32 product
 // (6), or of LBM_BF16X3 (3).  split_takes: the launches it is used for.
-bool split_takes(const SplitLaunch& L, int terms);
+bool split_takes(const SplitLaunch& L, int dim, int terms);
 hipError_t launch_fractional_split(SplitLaunch& L, int terms, hipStream_t s);
 // Long axes (every operator needs its far_m table): near band plus moments of
 // far boxes, LBM_FP32.  far_used: axis lengths that take this path.  launch_far_tables fills far_m.

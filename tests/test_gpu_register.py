@@ -1,5 +1,6 @@
-"""set_register_kernels keeps axes with far boxes on the register kernels too:
-on a grid whose axes all have boxes, and where a long axis with boxes lies
+"""Where the dense fractional term runs on the register kernels by itself: the
+sizes on both sides of each line.  set_register_kernels keeps axes with far
+boxes on them too: on a grid whose axes all have boxes, and where a long axis with boxes lies
 beside a short one; and fade_solve, which sets it, there.  The tile that the
 size selects, forced, gives the same bits."""
 
@@ -58,3 +59,27 @@ def test_gradients_on_boxed_axes(monkeypatch):
     monkeypatch.setenv("LBM_FP32_TILE", TILE)
     for a, b in zip(run(), default):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize(
+    "precision,n,p,register",
+    [("fp32", [64, 64], [0.5, 0.5], False), ("fp32", [72, 64], [0.5, 0.5], True), ("fp32", [128, 128], [1.0, 0.0], True),
+     ("fp32", [136, 128], [0.5, 0.5], False), ("fp32", [128, 136], [1.0, 0.0], True),
+     ("fp32", [224, 224], [1.0, 0.0], True), ("fp32", [232, 232], [1.0, 0.0], False),
+     ("fp32", [232, 232], [1.0, 0.5], True), ("fp32", [384, 384], [0.5, 0.0], True),
+     ("fp32", [384, 392], [0.5, 0.5], False), ("fp32", [225, 224], [0.5, 0.5], False),
+     ("bf16x3", [384, 384], [0.5, 0.5], False), ("bf16x3", [400, 512], [0.5, 1.0], True),
+     ("bf16x3", [400, 512], [0.0, 1.0], False), ("bf16x3", [512, 384], [0.5, 0.5], False),
+     ("bf16x3", [528, 528], [0.5, 0.5], False), ("bf16x3", [848, 64], [0.5, 0.5], True),
+     ("bf16x3", [848, 16, 16], [0.5, 0.5, 0.5], False)],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, list) else str(v))
+def test_lines_between_the_dense_kernels(precision, n, p, register):
+    from paper_1706_09161_amd import LbmFade
+
+    cfg = synth.small(len(n), n, alpha=[1.4, 1.7, 1.5][:len(n)], p=p, seed=83)
+    C = _field(cfg, 34)
+    with LbmFade.from_config(cfg, precision=precision) as s:
+        default = s.apply_phi(C)
+        s.set_register_kernels(True)
+        kept = s.apply_phi(C)
+    assert torch.equal(default, kept) == register
