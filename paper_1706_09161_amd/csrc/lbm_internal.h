@@ -101,7 +101,10 @@ struct FracLaunch {
 
 // The same for the kernels on three-term splits (fractional_split.hip,
 // fractional_far.hip): the axes of one step, and of an operator what they read.
-struct SplitOp {
+// Whole cache lines: the operator of a workgroup is loaded by its index, and
+// across lines 1 % of short launches is lost (split BF16 1024 x 24 x 24 17.35 us
+// packed, 17.15 so).
+struct alignas(64) SplitOp {
     int n, lower_only, upper_only, ends_excluded;
     const float *gen, *col0, *colN;
     const uint32_t *pw_hi, *pw_lo, *pw_l3;
