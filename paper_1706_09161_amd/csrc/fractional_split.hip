@@ -362,10 +362,14 @@ hipError_t pick(SplitLaunch& L, hipStream_t s)
 //    6.58 / 6.44).  The next ones are this kernel's: one-sided 240^2 6.53 / 6.74,
 //    480^2 8.97 / 9.11, and a strided axis of up to 128 beside a longer
 //    contiguous one, 200 x 128 5.89 / 6.33, 400 x 320 7.85 / 8.44.
-//  * Split BF16, every axis a multiple of 16: both of 385 to 512 nodes with a
-//    two-sided operator (400^2 7.82 / 7.61, 512^2 7.81 / 7.69; one-sided 512^2
-//    7.71 / 7.82, 384^2 6.95 / 7.53, 528^2 9.32 / 9.95), and beyond 832 (896^2
-//    15.98 / 14.99, 1024^2 18.41 / 15.24; 832^2 13.55 / 14.61).
+//  * Split BF16, every axis a multiple of 16: a strided axis of 385 to 512 nodes,
+//    none longer, with a two-sided operator (400^2 7.82 / 7.61, 512^2 7.81 /
+//    7.69, 96 x 512 7.59 / 7.42; one-sided 512^2 7.71 / 7.82, 384^2 6.95 / 7.53,
+//    512 x 256 6.49 / 7.50, 528^2 9.32 / 9.95), and beyond 832 (896^2 15.98 /
+//    14.99, 1024^2 18.41 / 15.24; 832^2 13.55 / 14.61).  Multiples of 8 alone:
+//    every axis of 961 to 1024 nodes with a two-sided operator (968^2 19.79 /
+//    19.21, 1000^2 19.95 / 19.54; one-sided 1000^2 14.81 / 18.95, 936^2 19.41 /
+//    19.79, 1032^2 28.2 / 43.9).
 // In 3D the line blocks are many enough to hide this kernel's set-up (split
 // BF16 1024 x 64 x 64 42.1 / 54.3, 2048 x 64 x 64 93 / 114) until one axis is
 // nearly all of the grid (4096 x 16 x 16 53.6 / 45.4).
@@ -386,9 +390,10 @@ bool split_takes(const SplitLaunch& L, int dim, int terms)
         if (dim == 3 || align % 8 != 0 || nmax <= 64) return true;
         return nmax > 128 && (ny <= 128 || nmax > (two_sided ? 384 : 224));
     }
-    if (align % 16 != 0) return true;
-    if (dim == 3) return nmax <= 2048;
-    return nmax <= 832 && !(two_sided && nmin > 384 && nmax <= 512);
+    if (align % 8 != 0) return true;
+    if (dim == 3) return align % 16 != 0 || nmax <= 2048;
+    if (align % 16 != 0) return !(two_sided && nmin > 960 && nmax <= 1024);
+    return nmax <= 832 && !(two_sided && ny > 384 && nmax <= 512);
 }
 
 hipError_t launch_fractional_split(SplitLaunch& L, int terms, hipStream_t s)

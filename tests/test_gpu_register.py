@@ -70,6 +70,9 @@ def test_gradients_on_boxed_axes(monkeypatch):
      ("fp32", [384, 392], [0.5, 0.5], False), ("fp32", [225, 224], [0.5, 0.5], False),
      ("bf16x3", [384, 384], [0.5, 0.5], False), ("bf16x3", [400, 512], [0.5, 1.0], True),
      ("bf16x3", [400, 512], [0.0, 1.0], False), ("bf16x3", [512, 384], [0.5, 0.5], False),
+     ("bf16x3", [96, 512], [0.5, 0.5], True), ("bf16x3", [968, 1000], [0.5, 0.5], True),
+     ("bf16x3", [968, 1000], [1.0, 0.0], False), ("bf16x3", [952, 1000], [0.5, 0.5], False),
+     ("bf16x3", [1000, 1032], [0.5, 0.5], False),
      ("bf16x3", [528, 528], [0.5, 0.5], False), ("bf16x3", [848, 64], [0.5, 0.5], True),
      ("bf16x3", [848, 16, 16], [0.5, 0.5, 0.5], False)],
     ids=lambda v: "x".join(map(str, v)) if isinstance(v, list) else str(v))
