@@ -174,9 +174,7 @@ LBM_API int lbm_fade_step(lbm_fade_t h, int64_t n, void* stream);
 LBM_API int lbm_fade_get_C(lbm_fade_t h, float* dst, int32_t on_device, void* stream);
 
 /* Copy / replace the populations (Q*nodes floats, structure of arrays) of the
- * current state (after streaming and the Dirichlet rule).  The populations are
- * the whole state: set_f recomputes C from them, and a run continued from saved
- * ones gives the results of the run they were saved from, bit for bit. */
+ * current state (after streaming and the Dirichlet rule).  set_f recomputes C. */
 LBM_API int lbm_fade_get_f(lbm_fade_t h, float* dst, int32_t on_device, void* stream);
 LBM_API int lbm_fade_set_f(lbm_fade_t h, const float* src, int32_t on_device, void* stream);
 

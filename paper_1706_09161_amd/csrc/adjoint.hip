@@ -426,7 +426,8 @@ struct AdjointState {
     int64_t nseg = 0;    // checkpoints allocated
     void* seg_mem[2] = {nullptr, nullptr};  // one allocation per segment buffer (the first also holds the checkpoints)
     void* fields = nullptr;                 // one allocation: fbar .. acc below
-    float* ckpt = nullptr;  // populations at the start of every segment
+    float* ckpt = nullptr;   // populations at the start of every segment
+    float* ckptC = nullptr;  // and C there, where the collision reads it (cc.moments)
     // recomputed segments, double-buffered (nbuf = 2) when both fit, so that
     // the next segment's recompute runs on a side stream during this
     // segment's reverse sweep
@@ -573,13 +574,13 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
     const int64_t nodes = h->nodes;
     const int Q = h->Q, d = h->dim;
     const int64_t nseg = (n + K - 1) / K > 0 ? (n + K - 1) / K : 1;
-    if (A->ckpt && A->K == K && A->nseg >= nseg) return true;
+    if (A->ckpt && A->K == K && A->nseg >= nseg && (A->ckptC || !h->cc.moments)) return true;
     for (int b = 0; b < 2; ++b) {
         (void)hipFree(A->seg_mem[b]);
         A->seg_mem[b] = nullptr;
         A->seg_f[b] = A->seg_phi[b] = A->seg_C[b] = nullptr;
     }
-    A->ckpt = nullptr;
+    A->ckpt = A->ckptC = nullptr;
     A->nbuf = 0;
     A->K = K;
     A->nseg = nseg;
@@ -587,7 +588,11 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
     for (int b = 0; b < 2; ++b) {
         Slab slab;
         const size_t of = slab.take(fq * (K + 1)), op = slab.take(field * d * K), oC = slab.take(field * K);
-        const size_t ock = b == 0 ? slab.take(fq * nseg) : 0;
+        size_t ock = 0, ockC = 0;
+        if (b == 0) {
+            ock = slab.take(fq * nseg);
+            if (h->cc.moments) ockC = slab.take(field * nseg);
+        }
         if (hipMalloc(&A->seg_mem[b], slab.bytes) != hipSuccess) {
             // a second buffer is an optimisation: run single-buffered without it
             (void)hipGetLastError();
@@ -599,7 +604,10 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
         A->seg_f[b] = reinterpret_cast<float*>(base + of);
         A->seg_phi[b] = reinterpret_cast<float*>(base + op);
         A->seg_C[b] = reinterpret_cast<float*>(base + oC);
-        if (b == 0) A->ckpt = reinterpret_cast<float*>(base + ock);
+        if (b == 0) {
+            A->ckpt = reinterpret_cast<float*>(base + ock);
+            if (h->cc.moments) A->ckptC = reinterpret_cast<float*>(base + ockC);
+        }
         A->nbuf = b + 1;
     }
     if (!A->side) {
@@ -724,7 +732,11 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     };
     auto recompute = [&](int64_t sg, int b, hipStream_t st) -> int {
         const int len = seg_len(sg);
-        ADJ_TRY(launch_moment(h->cc, f_of(sg, b, 0), A->seg_C[b], st));
+        if (h->cc.moments)
+            ADJ_TRY(hipMemcpyAsync(A->seg_C[b], A->ckptC + sg * nodes, sizeof(float) * nodes,
+                                   hipMemcpyDeviceToDevice, st));
+        else
+            ADJ_TRY(launch_moment(h->cc, f_of(sg, b, 0), A->seg_C[b], st));
         for (int j = 0; j < len; ++j) {
             float* phi_j = A->seg_phi[b] + (int64_t)j * d * nodes;
             int rc = fade_run_phi(h, A->seg_C[b] + (int64_t)j * nodes, phi_j, st);
@@ -733,8 +745,8 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
                 return rc;
             }
             if (j + 1 < len)
-                ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, j), A->seg_f[b] + (int64_t)(j + 1) * Q * nodes,
-                                              phi_j, h->S, A->seg_C[b] + (int64_t)(j + 1) * nodes, st));
+                ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, j), A->seg_C[b] + (int64_t)j * nodes,
+                                              A->seg_f[b] + (int64_t)(j + 1) * Q * nodes, phi_j, h->S, A->seg_C[b] + (int64_t)(j + 1) * nodes, st));
         }
         return LBM_OK;
     };
@@ -747,12 +759,17 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     // --- forward pass with checkpoints (the handle's state advances to step n).
     // The last segment runs as its own recompute, into the buffer the reverse
     // sweep reads first, and its last step from there: the same kernels on the
-    // same inputs as the plain step (the moment kernel and the collide-stream
-    // kernel sum C in the same order), so the state is the same.
+    // same inputs as the plain step (C kept with the checkpoint, or summed by
+    // the moment kernel in the collide-stream kernel's order), so the state is
+    // the same.
     const int64_t t_last = (nseg - 1) * K;  // first step of the last segment
     for (int64_t t = 0; t < n; ++t) {
-        if (t % K == 0) ADJ_TRY(hipMemcpyAsync(A->ckpt + (t / K) * Q * nodes, h->f[h->cur], fq,
-                                               hipMemcpyDeviceToDevice, s));
+        if (t % K == 0) {
+            ADJ_TRY(hipMemcpyAsync(A->ckpt + (t / K) * Q * nodes, h->f[h->cur], fq, hipMemcpyDeviceToDevice, s));
+            if (h->cc.moments)
+                ADJ_TRY(hipMemcpyAsync(A->ckptC + (t / K) * nodes, h->C[h->cur], sizeof(float) * nodes,
+                                       hipMemcpyDeviceToDevice, s));
+        }
         if (t == t_last) break;
         int rc = fade_forward_step(h, s);
         if (rc) {
@@ -766,8 +783,9 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
         const int b = buf_of(sg), len = seg_len(sg);
         int rc = recompute(sg, b, s);
         if (rc) return rc;
-        ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, len - 1), h->f[1 - h->cur],
-                                      A->seg_phi[b] + (int64_t)(len - 1) * d * nodes, h->S, h->C, s));
+        ADJ_TRY(launch_collide_stream(h->cc, f_of(sg, b, len - 1), A->seg_C[b] + (int64_t)(len - 1) * nodes,
+                                      h->f[1 - h->cur], A->seg_phi[b] + (int64_t)(len - 1) * d * nodes, h->S,
+                                      h->C[1 - h->cur], s));
         h->cur = 1 - h->cur;
         h->steps_done += len;
         h->at_initial_C = false;

@@ -239,28 +239,23 @@ __device__ inline void collide_x_pair(const CollideConsts& cc, const float (&f)[
 // small differences added to C once: f*_0, the largest population of the
 // opposite sign, does not enter, and neither do the roundings of a sum with
 // it.  They are alike from step to step where C changes slowly, and a C summed
-// from pulled populations and f*_0 drifts with them (2D, 64 x 64, 200 steps:
-// 2.7e-6 of C against 4.6e-7 so and 7.8e-7 with the operator R).
-// The new f_0 is C' less the other populations, and the node's C is put back
-// together from it (moment_of: C' itself wherever f_0 has no coarser unit), so
-// the populations are the whole state: a run continued from saved ones has the
-// bits of the run they were saved from.
-// Between two steps of one run the state is C and j (1 + d fields) in
+// from the populations drifts with them (2D, 64 x 64, 200 steps: 2.7e-6 of C
+// against 4.6e-7 so and 7.8e-7 with the operator R).
+// Between two steps of one run the state is then C and j (1 + d fields) in
 // place of the populations: a step reads 1 + 2 d values a node and writes
-// 1 + d, 8 instead of 13 in 2D and 11 instead of 18 in 3D.  Errors against 64
-// bits (relative L2 of C, wall value 0, operator R / moments, and moments with
-// C kept beside the populations instead): 129 x 200 with a source, 1000 steps
-// 8.8e-6 / 2.3e-6 / 2.0e-6, 256^2 100 steps 2.3e-6 / 1.9e-6 / 1.4e-6, 45^3 60
-// steps 3.5e-7 / 3.0e-7 / 2.5e-7.
+// 1 + d, 8 instead of 13 in 2D and 11 instead of 18 in 3D.  From populations
+// these forms take f_1 .. and C, not f_0.  Errors against 64 bits (relative L2
+// of C, operator R / moments): 129 x 200 with a source, 1000 steps 8.6e-6 /
+// 4.2e-6, 256^2 100 steps 5.3e-6 / 5.0e-6, 45^3 60 steps 1.97e-6 / 1.94e-6.
 //
 // FORM of a kernel: how it collides and what its state is made of.  The three
 // moment forms and kMomentCollision round alike: j is the same difference of
 // the same values, whether stored or formed again.
 constexpr int kPopulations = 0;      // collision operator R, populations in and out
-constexpr int kMomentCollision = 1;  // collision in moments, populations in and out
-constexpr int kToMoments = 2;        // populations in, moments out
+constexpr int kMomentCollision = 1;  // collision in moments, populations and C in and out
+constexpr int kToMoments = 2;        // populations and C in, moments out
 constexpr int kMoments = 3;          // moments in and out
-constexpr int kFromMoments = 4;      // moments in, populations out
+constexpr int kFromMoments = 4;      // moments in, populations and C out
 template <int FORM>
 constexpr bool reads_moments = FORM >= kMoments;
 template <int FORM>
@@ -268,32 +263,12 @@ constexpr bool writes_moments = FORM == kToMoments || FORM == kMoments;
 template <int Q, int FORM>
 constexpr int fields_in = reads_moments<FORM> ? (Q + 1) / 2 : Q;
 
-// Sum of the moving populations, pairs first.
-template <int Q>
-__device__ __forceinline__ float moving_sum(const float (&f)[Q])
-{
-#pragma clang fp contract(off)
-    float s = 0.f;
-#pragma unroll
-    for (int i = 1; i < Q; i += 2) s += f[i] + f[i + 1];
-    return s;
-}
-
-// C of a node's populations where the collision is in moments: every kernel
-// that forms it there adds in this order.
-template <int Q>
-__device__ __forceinline__ float moment_of(const float (&f)[Q])
-{
-    return f[0] + moving_sum<Q>(f);
-}
-
-// C and j of a node from its input fields (populations, or C and j)
+// C and j of a node from its input fields (C, then f_1 .. or j)
 template <int Q, int FORM>
 __device__ __forceinline__ void moments_of(const float (&v)[fields_in<Q, FORM>], float& C, float (&j)[(Q - 1) / 2])
 {
     constexpr int d = (Q - 1) / 2;
-    if constexpr (reads_moments<FORM>) C = v[0];
-    else C = moment_of<Q>(v);
+    C = v[0];
 #pragma unroll
     for (int a = 0; a < d; ++a) {
         if constexpr (reads_moments<FORM>) j[a] = v[1 + a];
@@ -377,15 +352,21 @@ __device__ __forceinline__ void finish_node(const float (&fs)[Q], float (&f)[Q],
     int nu = 0;
 #pragma unroll
     for (int i = 1; i < Q; ++i) nu += unk[i];
-    if constexpr (FORM == kPopulations) {
-        f[0] = fs[0];
-    } else if (nu > 0) {
-        f[0] = fs[0] - moving_sum<Q>(fs);
-    } else {
+    float c;
+    if constexpr (FORM != kPopulations) {
         float dc = 0.f;
 #pragma unroll
         for (int a = 0; a < d; ++a) dc += (f[2 * a + 1] - fs[2 * a + 1]) + (f[2 * a + 2] - fs[2 * a + 2]);
-        f[0] = (fs[0] + dc) - moving_sum<Q>(f);
+        c = fs[0] + dc;
+    }
+    if (FORM == kPopulations || !writes_moments<FORM> || nu > 0) {
+        f[0] = fs[0];
+        if constexpr (FORM != kPopulations) {
+            float s = 0.f;
+#pragma unroll
+            for (int a = 0; a < d; ++a) s += fs[2 * a + 1] + fs[2 * a + 2];
+            f[0] = fs[0] - s;
+        }
     }
     if (nu > 0) {
         float known = f[0];
@@ -398,13 +379,10 @@ __device__ __forceinline__ void finish_node(const float (&fs)[Q], float (&f)[Q],
             if (unk[i]) f[i] = share;
     }
     if (!stored) return;
-    float c;
-    if constexpr (FORM == kPopulations) {
+    if (FORM == kPopulations || nu > 0) {
         c = f[0];
 #pragma unroll
         for (int i = 1; i < Q; ++i) c += f[i];
-    } else {
-        c = moment_of<Q>(f);
     }
     if constexpr (writes_moments<FORM>) {
         store(0, c);
@@ -422,7 +400,7 @@ __device__ __forceinline__ void finish_node(const float (&fs)[Q], float (&f)[Q],
 // is collided, the loads of rows y + 2 .. y + D are in flight.
 template <int FORM, bool HAS_S, bool VAR, bool NT, typename OFF>
 __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const float* __restrict__ fin,
-                                                         float* __restrict__ fout, const float* __restrict__ Phi,
+                                                         const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                          const float* __restrict__ S, float* __restrict__ Cout,
                                                          int rows_per_wave, int strips, int total_waves)
 {
@@ -444,6 +422,7 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
     const float* fi[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) fi[i] = fin + i * nodes;
+    if (FORM == kMomentCollision || FORM == kToMoments) fi[0] = Cin;
     const float* ph1 = Phi + nodes;
     const float* dbk[3];  // VAR: the three fields of dB (00, 01, 11)
 #pragma unroll
@@ -547,7 +526,7 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
 // parity so one barrier per plane suffices.
 template <int FORM, int NY, bool HAS_S, bool VAR, bool NT, typename OFF>
 __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, const float* __restrict__ fin,
-                                                             float* __restrict__ fout, const float* __restrict__ Phi,
+                                                             const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                              const float* __restrict__ S, float* __restrict__ Cout,
                                                              int planes_per_block, int strips_x, int strips_y)
 {
@@ -580,6 +559,7 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
     // one base per array and field offsets added per load (keeps the scalar
     // registers for the collision operator)
     const OFF fb = (OFF)(nodes * 4);  // bytes per field
+    const float* in0 = FORM == kMomentCollision || FORM == kToMoments ? Cin : fin;
 
     struct Plane {
         float f[NI], phi[3], s;
@@ -594,12 +574,12 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
         const int64_t zoff = (int64_t)min(max(z, 0), nz - 1) * plane;
         const OFF bm = (OFF)((zoff + xyc) * 4), bh = (OFF)((zoff + xyh) * 4);
 #pragma unroll
-        for (int i = 0; i < NI; ++i) p.f[i] = ldf(fin, bm + i * fb);
+        for (int i = 0; i < NI; ++i) p.f[i] = i == 0 ? ldf(in0, bm) : ldf(fin, bm + i * fb);
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) p.phi[mu] = ldf(Phi, bm + mu * fb);
         p.s = HAS_S ? ldf(S, bm) : 0.f;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) p.h[i] = ldf(fin, bh + i * fb);
+        for (int i = 0; i < NI; ++i) p.h[i] = i == 0 ? ldf(in0, bh) : ldf(fin, bh + i * fb);
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) p.hphi[mu] = ldf(Phi, bh + mu * fb);
         p.hs = HAS_S ? ldf(S, bh) : 0.f;
@@ -670,18 +650,6 @@ __global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, c
 }
 
 // ---------------------------------------------------------------------------
-// C of populations in the order of the handle's collision: the same bits as the
-// collide-stream kernels give the node's C.
-template <int Q>
-__device__ __forceinline__ float moment_as_collided(const CollideConsts& cc, const float (&f)[Q])
-{
-    if (cc.moments) return moment_of<Q>(f);
-    float c = 0.f;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) c += f[i];
-    return c;
-}
-
 // f := f^eq(C, Phi) and C := <1|f> at every node (initial state).  Bound by
 // HBM, 1 + d values read and 1 + Q written a node; the moment of the rounded
 // populations costs nothing here and a pass of its own otherwise (4096^2 75 +
@@ -710,9 +678,13 @@ __global__ void equilibrium_init(CollideConsts cc, float* __restrict__ C, const 
         v[2 * mu + 1] = a + b;
         v[2 * mu + 2] = a - b;
     }
+    float m = 0.f;  // in the order of moment_kernel
 #pragma unroll
-    for (int i = 0; i < Q; ++i) f[i * nodes + x] = v[i];
-    C[x] = moment_as_collided<Q>(cc, v);
+    for (int i = 0; i < Q; ++i) {
+        f[i * nodes + x] = v[i];
+        m += v[i];
+    }
+    C[x] = m;
 }
 
 // C := the Dirichlet values on the faces of the box.  One thread per node of a
@@ -744,15 +716,16 @@ __global__ void fill_kernel(float* __restrict__ p, int64_t count, float v)
 }
 
 template <int Q>
-__global__ void moment_kernel(CollideConsts cc, const float* __restrict__ f, float* __restrict__ C, int64_t nodes)
+__global__ void moment_kernel(const float* __restrict__ f, float* __restrict__ C, int64_t nodes)
 {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= nodes) return;
-    float v[Q];
+    float c = 0.f;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) v[i] = f[i * nodes + x];
-    C[x] = moment_as_collided<Q>(cc, v);
+    for (int i = 0; i < Q; ++i) c += f[i * nodes + x];
+    C[x] = c;
 }
+
 
 __global__ void nonfinite_kernel(const float* __restrict__ C, int64_t nodes, int* flag)
 {
@@ -802,8 +775,8 @@ int collide_rows_override()
 
 bool moment_runs(const CollideConsts& cc) { return cc.moments && nodes_of(cc) * 7 * 4 < ((int64_t)1 << 32); }
 
-hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, float* f_out, const float* Phi,
-                                 const float* S, float* C_out, hipStream_t s, StepState state)
+hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, const float* C_in, float* f_out,
+                                 const float* Phi, const float* S, float* C_out, hipStream_t s, StepState state)
 {
     // 32-bit byte offsets while every array (at most 7 fields of the node count) fits in 4 GiB
     const bool small = nodes_of(cc) * 7 * 4 < ((int64_t)1 << 32);
@@ -811,6 +784,8 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, flo
     const bool var = cc.dB != nullptr;
     if (var && !cc.Cw) return hipErrorInvalidValue;
     if (state != StepState::populations && !moment_runs(cc)) return hipErrorInvalidValue;
+    // C is read at neighbouring nodes too while it is written
+    if (state == StepState::populations && cc.moments && C_in == C_out) return hipErrorInvalidValue;
     const bool in_m = state == StepState::moments || state == StepState::to_populations;
     const bool out_m = state == StepState::moments || state == StepState::to_moments;
     // Non-temporal output stores once a step's traffic exceeds the 256 MB
@@ -853,7 +828,8 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, flo
         const int waves = strips * chunks;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
         auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, cc, f_in, f_out, Phi, S, C_out, rows, strips, waves);
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, rows, strips,
+                               waves);
         };
         with_form([&](auto form, auto hs, auto vr, auto ntc) {
             constexpr bool HS = decltype(hs)::value, VR = decltype(vr)::value, NT = decltype(ntc)::value;
@@ -913,8 +889,8 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, flo
         if constexpr (F <= kMomentCollision) {
             if (!small) kern = collide_stream_3d<F, NY, HS, VR, NT, uint64_t>;
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, cc, f_in, f_out, Phi, S, C_out, planes, sx,
-                           sy);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, planes,
+                           sx, sy);
         return hipSuccess;
     };
     hipError_t e = hipSuccess;
@@ -958,9 +934,9 @@ hipError_t launch_moment(const CollideConsts& cc, const float* f, float* C, hipS
 {
     const int64_t nodes = nodes_of(cc);
     if (cc.Q == 5)
-        hipLaunchKernelGGL(moment_kernel<5>, dim3(blocks_for(nodes, 256)), dim3(256), 0, s, cc, f, C, nodes);
+        hipLaunchKernelGGL(moment_kernel<5>, dim3(blocks_for(nodes, 256)), dim3(256), 0, s, f, C, nodes);
     else
-        hipLaunchKernelGGL(moment_kernel<7>, dim3(blocks_for(nodes, 256)), dim3(256), 0, s, cc, f, C, nodes);
+        hipLaunchKernelGGL(moment_kernel<7>, dim3(blocks_for(nodes, 256)), dim3(256), 0, s, f, C, nodes);
     return hipGetLastError();
 }
 

@@ -352,9 +352,10 @@ int run_phi(lbm_fade* h, const float* C, float* Phi, hipStream_t s)
 
 int forward_step(lbm_fade* h, hipStream_t s)
 {
-    int rc = run_phi(h, h->C, h->Phi, s);
+    int rc = run_phi(h, h->C[h->cur], h->Phi, s);
     if (rc) return rc;
-    HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->f[1 - h->cur], h->Phi, h->S, h->C, s));
+    HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi, h->S,
+                                       h->C[1 - h->cur], s));
     h->cur = 1 - h->cur;
     h->steps_done += 1;
     h->at_initial_C = false;
@@ -378,14 +379,15 @@ int run_steps(lbm_fade* h, int64_t n, hipStream_t s)
         }
         return LBM_OK;
     }
-    const float* C = h->C;
+    const float* C = h->C[h->cur];
     h->has_state = false;  // until the populations are back
     for (int64_t k = 0; k < n; ++k) {
         const int rc = run_phi(h, C, h->Phi, s);
         if (rc) return rc;
         const lbm::StepState st = k == 0 ? lbm::StepState::to_moments
                                          : (k == n - 1 ? lbm::StepState::to_populations : lbm::StepState::moments);
-        HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->f[1 - h->cur], h->Phi, h->S, h->C, s, st));
+        HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi, h->S,
+                                           h->C[1 - h->cur], s, st));
         h->cur = 1 - h->cur;
         C = h->f[h->cur];  // field 0 of the moments
     }
@@ -461,7 +463,7 @@ int build_step_graph(lbm_fade* h)
 // C := sum_i f_i of the current populations
 int refresh_C(lbm_fade* h, hipStream_t s)
 {
-    HIP_TRY(lbm::launch_moment(h->cc, h->f[h->cur], h->C, s));
+    HIP_TRY(lbm::launch_moment(h->cc, h->f[h->cur], h->C[h->cur], s));
     return LBM_OK;
 }
 
@@ -800,7 +802,8 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     lbm::Slab slab;
     slab.take(bytes);
     const size_t of0 = slab.take(field * Q), of1 = slab.take(field * Q);
-    const size_t oC = slab.take(field), oPhi = slab.take(field * d), oflag = slab.take(sizeof(int) * 4);
+    const size_t oC = slab.take(field), oC1 = h->free_times_one ? slab.take(field) : oC;
+    const size_t oPhi = slab.take(field * d), oflag = slab.take(sizeof(int) * 4);
     hipError_t e = hipMalloc(&h->mem, slab.bytes);
     if (e != hipSuccess) {
         cleanup();
@@ -810,7 +813,8 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
     h->f[0] = at(of0);
     h->f[1] = at(of1);
-    h->C = at(oC);
+    h->C[0] = at(oC);
+    h->C[1] = at(oC1);
     h->Phi = at(oPhi);
     h->flag = reinterpret_cast<int*>(base + oflag);
     std::vector<unsigned char> host(upload, 0);
@@ -854,11 +858,11 @@ int lbm_fade_set_C(lbm_fade_t h, const float* C0, int32_t on_device, void* strea
     int rc = check_device(h);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(h->C, C0, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
-    HIP_TRY(lbm::launch_wall_overwrite(h->cc, h->C, s));
-    rc = run_phi(h, h->C, h->Phi, s);
+    HIP_TRY(hipMemcpyAsync(h->C[h->cur], C0, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
+    HIP_TRY(lbm::launch_wall_overwrite(h->cc, h->C[h->cur], s));
+    rc = run_phi(h, h->C[h->cur], h->Phi, s);
     if (rc) return rc;
-    HIP_TRY(lbm::launch_equilibrium_init(h->cc, h->C, h->Phi, h->f[h->cur], s));
+    HIP_TRY(lbm::launch_equilibrium_init(h->cc, h->C[h->cur], h->Phi, h->f[h->cur], s));
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));  // the host buffer may be reused on return
     h->has_state = true;
     h->at_initial_C = true;
@@ -954,16 +958,7 @@ int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on)
         drop_graph(h);
     }
     h->register_kernels = on != 0;
-    const int moments = h->free_times_one && !h->register_kernels;
-    if (moments != h->cc.moments && h->has_state) {
-        // C as the collision now in use adds it up
-        HIP_TRY(hipDeviceSynchronize());
-        h->cc.moments = moments;
-        rc = refresh_C(h, nullptr);
-        if (rc) return rc;
-        HIP_TRY(hipDeviceSynchronize());
-    }
-    h->cc.moments = moments;
+    h->cc.moments = h->free_times_one && !h->register_kernels;
     return LBM_OK;
 }
 
@@ -1004,7 +999,7 @@ int lbm_fade_step(lbm_fade_t h, int64_t n, void* stream)
         if (every > 0 && h->steps_done % every == 0) {
             int flag = 0;
             HIP_TRY(hipMemsetAsync(h->flag, 0, sizeof(int), s));
-            HIP_TRY(lbm::launch_nonfinite_check(h->C, h->nodes, h->flag, s));
+            HIP_TRY(lbm::launch_nonfinite_check(h->C[h->cur], h->nodes, h->flag, s));
             HIP_TRY(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
             if (flag) {
@@ -1024,7 +1019,7 @@ int lbm_fade_get_C(lbm_fade_t h, float* dst, int32_t on_device, void* stream)
     int rc = check_device(h);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(dst, h->C, sizeof(float) * h->nodes, kind_from_dev(on_device), s));
+    HIP_TRY(hipMemcpyAsync(dst, h->C[h->cur], sizeof(float) * h->nodes, kind_from_dev(on_device), s));
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));
     return LBM_OK;
 }
@@ -1067,7 +1062,7 @@ int lbm_fade_apply_phi(lbm_fade_t h, const float* C, float* Phi, int32_t on_devi
         // the solver's own concentration
         if (!h->has_state) return fail(LBM_ESTATE, "no state yet");
         if (!on_device) return fail(LBM_EINVAL, "C = NULL needs a device Phi");
-        return run_phi(h, h->C, Phi, s);
+        return run_phi(h, h->C[h->cur], Phi, s);
     }
     if (on_device) return run_phi(h, C, Phi, s);
     float *dC = nullptr, *dP = nullptr;

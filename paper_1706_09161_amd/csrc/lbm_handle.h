@@ -19,7 +19,10 @@ struct lbm_fade {
     int device = 0;
     float* f[2] = {nullptr, nullptr};
     int cur = 0;  // f[cur] holds the current populations
-    float* C = nullptr;  // their moment
+    // C[cur]: their moment.  Two fields where the collision reads C
+    // (free_times_one: it writes C while neighbours still read it), one field
+    // otherwise (C[0] == C[1]).
+    float* C[2] = {nullptr, nullptr};
     float* Phi = nullptr;
     float* S = nullptr;
     // space-dependent coefficients (allocated together on first use; cc.dB / cc.Cw

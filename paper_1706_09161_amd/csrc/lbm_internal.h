@@ -169,13 +169,15 @@ struct Slab {
 };
 
 // One step's collision, streaming and walls.  The state read and written is
-// the populations (with their moment written to C_out), or, inside a run of
-// steps where moment_runs(), the 1 + d fields C, j_0, .. of the collision in
-// moments (consecutive node fields in the same buffers; C_out is not written).
+// the populations and C (C_in is read only where cc.moments, and must not be
+// C_out then), or, inside a run of steps where moment_runs(), the 1 + d fields
+// C, j_0, .. of the collision in moments (consecutive node fields in the same
+// buffers; C_in is not read then, C_out not written).
 enum class StepState { populations, to_moments, moments, to_populations };
 bool moment_runs(const CollideConsts& cc);
-hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, float* f_out, const float* Phi,
-                                 const float* S, float* C_out, hipStream_t s, StepState state = StepState::populations);
+hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, const float* C_in, float* f_out,
+                                 const float* Phi, const float* S, float* C_out, hipStream_t s,
+                                 StepState state = StepState::populations);
 // f := f^eq(C, Phi), C := <1|f>
 hipError_t launch_equilibrium_init(const CollideConsts& cc, float* C, const float* Phi, float* f, hipStream_t s);
 hipError_t launch_wall_overwrite(const CollideConsts& cc, float* C, hipStream_t s);
