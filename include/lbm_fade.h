@@ -174,9 +174,20 @@ LBM_API int lbm_fade_step(lbm_fade_t h, int64_t n, void* stream);
 LBM_API int lbm_fade_get_C(lbm_fade_t h, float* dst, int32_t on_device, void* stream);
 
 /* Copy / replace the populations (Q*nodes floats, structure of arrays) of the
- * current state (after streaming and the Dirichlet rule).  set_f recomputes C. */
+ * current state (after streaming and the Dirichlet rule).  set_f makes C their
+ * sum.  A run that goes on from saved populations alone goes on bit for bit for
+ * BGK, for MRT with a free relaxation time other than 1 and with
+ * set_register_kernels on, where C is that sum.  For MRT with every free time 1
+ * the steps carry C on its own, more exactly than the sum of the rounded
+ * populations: f and C (get_C) are the state there, and lbm_fade_set_state
+ * restores both. */
 LBM_API int lbm_fade_get_f(lbm_fade_t h, float* dst, int32_t on_device, void* stream);
 LBM_API int lbm_fade_set_f(lbm_fade_t h, const float* src, int32_t on_device, void* stream);
+
+/* Replace the state by saved populations f (get_f) and their concentration C
+ * (get_C; nodes floats): a run goes on from there as the one they were saved
+ * from, bit for bit.  C = NULL: as lbm_fade_set_f. */
+LBM_API int lbm_fade_set_state(lbm_fade_t h, const float* f, const float* C, int32_t on_device, void* stream);
 
 /* Apply the fractional operator of Sec. 2.4 to a given field:
  * Phi[mu*nodes + node] = p_mu I+(g_mu C) + (1-p_mu) I-(g_mu C) for every axis,

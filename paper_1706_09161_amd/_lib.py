@@ -20,7 +20,7 @@ ERROR_NAMES = {LBM_EINVAL: "LBM_EINVAL", LBM_ENOMEM: "LBM_ENOMEM", LBM_EDEVICE: 
 # Every symbol include/lbm_fade.h declares.
 EXPORTED = ["lbm_fade_create", "lbm_fade_destroy", "lbm_fade_set_C", "lbm_fade_set_source", "lbm_fade_set_diffusion",
             "lbm_fade_set_register_kernels", "lbm_fade_set_wall", "lbm_fade_step",
-            "lbm_fade_get_C", "lbm_fade_get_f", "lbm_fade_set_f", "lbm_fade_apply_phi", "lbm_fade_apply_phi_noalloc",
+            "lbm_fade_get_C", "lbm_fade_get_f", "lbm_fade_set_f", "lbm_fade_set_state", "lbm_fade_apply_phi", "lbm_fade_apply_phi_noalloc",
             "lbm_fade_adjoint",
             "lbm_fade_last_error", "lbm_fade_version", "lbm_rw_init_gaussian", "lbm_rw_walk", "lbm_rw_histogram"]
 
@@ -99,6 +99,7 @@ def lib() -> ctypes.CDLL:
         "lbm_fade_get_C": (ctypes.c_int, [H, fp, ctypes.c_int32, vp]),
         "lbm_fade_get_f": (ctypes.c_int, [H, fp, ctypes.c_int32, vp]),
         "lbm_fade_set_f": (ctypes.c_int, [H, fp, ctypes.c_int32, vp]),
+        "lbm_fade_set_state": (ctypes.c_int, [H, fp, fp, ctypes.c_int32, vp]),
         "lbm_fade_apply_phi": (ctypes.c_int, [H, fp, fp, ctypes.c_int32, vp]),
         "lbm_fade_apply_phi_noalloc": (ctypes.c_int, [ctypes.POINTER(lbm_grid), ctypes.POINTER(lbm_params), fp, fp,
                                                       vp]),

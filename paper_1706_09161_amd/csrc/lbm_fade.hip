@@ -1038,13 +1038,22 @@ int lbm_fade_get_f(lbm_fade_t h, float* dst, int32_t on_device, void* stream)
 
 int lbm_fade_set_f(lbm_fade_t h, const float* src, int32_t on_device, void* stream)
 {
-    if (!h || !src) return fail(LBM_EINVAL, "null argument");
+    return lbm_fade_set_state(h, src, nullptr, on_device, stream);
+}
+
+int lbm_fade_set_state(lbm_fade_t h, const float* f, const float* C, int32_t on_device, void* stream)
+{
+    if (!h || !f) return fail(LBM_EINVAL, "null argument");
     int rc = check_device(h);
     if (rc) return rc;
     hipStream_t s = as_stream(stream);
-    HIP_TRY(hipMemcpyAsync(h->f[h->cur], src, sizeof(float) * h->Q * h->nodes, kind_to_dev(on_device), s));
-    rc = refresh_C(h, s);
-    if (rc) return rc;
+    HIP_TRY(hipMemcpyAsync(h->f[h->cur], f, sizeof(float) * h->Q * h->nodes, kind_to_dev(on_device), s));
+    if (C) {
+        HIP_TRY(hipMemcpyAsync(h->C[h->cur], C, sizeof(float) * h->nodes, kind_to_dev(on_device), s));
+    } else {
+        rc = refresh_C(h, s);
+        if (rc) return rc;
+    }
     if (!on_device) HIP_TRY(hipStreamSynchronize(s));
     h->has_state = true;
     h->at_initial_C = false;

@@ -210,9 +210,17 @@ class LbmFade:
         L.check(L.lib().lbm_fade_get_f(self._h, ptr, dev, _stream_ptr(stream)))
         return out
 
-    def set_f(self, f, stream=None):
+    def set_f(self, f, stream=None, C=None):
+        """Replace the populations; C becomes their sum, or the C saved with them
+        (get_C), which a run needs to go on bit for bit where it is not that sum
+        (MRT with every free relaxation time 1).  f and C on the same side."""
         ptr, dev, keep = self._in(f, self.Q * self.nodes)
-        L.check(L.lib().lbm_fade_set_f(self._h, ptr, dev, _stream_ptr(stream)))
+        cptr = None
+        if C is not None:
+            cptr, cdev, ckeep = self._in(C, self.nodes)
+            if cdev != dev:
+                raise ValueError("f and C must both be host or both be device buffers")
+        L.check(L.lib().lbm_fade_set_state(self._h, ptr, cptr, dev, _stream_ptr(stream)))
 
     def apply_phi(self, C, out=None, stream=None):
         """Phi of every axis for the field C; C = None uses the solver's own
