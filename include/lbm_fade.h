@@ -166,8 +166,13 @@ LBM_API int lbm_fade_set_wall(lbm_fade_t h, const float* Cw, int32_t on_device, 
 LBM_API int lbm_fade_set_register_kernels(lbm_fade_t h, int32_t on);
 
 /* Advance n >= 0 time steps.  Asynchronous; the launches of one step are: the
- * fractional-term GEMM of every axis, then the fused collide-stream-boundary-
- * moment kernel.  Returns LBM_ESTATE before set_C/set_f. */
+ * fractional term of every axis (one launch, or two where a grid mixes long axes,
+ * summed through boxes, with short ones), then the fused collide-stream-boundary-
+ * moment kernel.  Returns LBM_ESTATE before set_C/set_f.  A launch that fails
+ * (LBM_EDEVICE) at the start of a call leaves the state as it was; one that fails
+ * later leaves the state of the last whole step, or none (LBM_ESTATE until
+ * set_C / set_f) for MRT with every free relaxation time 1, whose steps within a
+ * call do not store the populations. */
 LBM_API int lbm_fade_step(lbm_fade_t h, int64_t n, void* stream);
 
 /* Copy C (nodes floats) to host or device memory. */
@@ -193,7 +198,7 @@ LBM_API int lbm_fade_set_state(lbm_fade_t h, const float* f, const float* C, int
  * Phi[mu*nodes + node] = p_mu I+(g_mu C) + (1-p_mu) I-(g_mu C) for every axis,
  * with the handle's precision.  C and Phi are host or device (same on_device).
  * C = NULL applies it to the solver's current concentration (device Phi only;
- * LBM_ESTATE before set_C/set_f): exactly the GEMM launch of a step.
+ * LBM_ESTATE before set_C/set_f): exactly the launches of a step.
  * Does not touch the solver state. */
 LBM_API int lbm_fade_apply_phi(lbm_fade_t h, const float* C, float* Phi, int32_t on_device, void* stream);
 

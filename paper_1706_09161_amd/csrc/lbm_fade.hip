@@ -380,18 +380,26 @@ int run_steps(lbm_fade* h, int64_t n, hipStream_t s)
         return LBM_OK;
     }
     const float* C = h->C[h->cur];
-    h->has_state = false;  // until the populations are back
+    const int first = h->cur;
+    // A launch that fails leaves the state before the run, whose populations and
+    // C the first step only reads; once the second step's collision is queued
+    // they are gone, and so is the state.
+    auto failed = [&](int64_t k, int rc) {
+        h->cur = first;
+        h->has_state = k < 2;
+        return rc;
+    };
     for (int64_t k = 0; k < n; ++k) {
         const int rc = run_phi(h, C, h->Phi, s);
-        if (rc) return rc;
+        if (rc) return failed(k, rc);
         const lbm::StepState st = k == 0 ? lbm::StepState::to_moments
                                          : (k == n - 1 ? lbm::StepState::to_populations : lbm::StepState::moments);
-        HIP_TRY(lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi, h->S,
-                                           h->C[1 - h->cur], s, st));
+        const hipError_t e = lbm::launch_collide_stream(h->cc, h->f[h->cur], h->C[h->cur], h->f[1 - h->cur], h->Phi,
+                                                        h->S, h->C[1 - h->cur], s, st);
+        if (e != hipSuccess) return failed(k, fail(LBM_EDEVICE, std::string("collide-stream: ") + hipGetErrorString(e)));
         h->cur = 1 - h->cur;
         C = h->f[h->cur];  // field 0 of the moments
     }
-    h->has_state = true;
     h->steps_done += n;
     h->at_initial_C = false;
     return LBM_OK;
