@@ -107,7 +107,9 @@ enum { LBM_FLUX_RL = 0, LBM_FLUX_CAPUTO = 1 };
  * M^-1 Lambda M (equations (MatrixD2), (MatrixS)); the product-rule weights
  * c+-_{ln}(gamma_mu) of equations (c+), (c-) scaled by dx^gamma/Gamma(2+gamma),
  * as one Toeplitz generator per axis plus two boundary columns.
- * Allocates the device state (two population buffers, C, Phi, weights).
+ * Allocates the device state (two population buffers, C, Phi, weights; a second
+ * C for MRT with every free relaxation time 1, whose collision otherwise falls
+ * back to the one of other times).
  * The product-rule integrals over the empty intervals at the ends of a line
  * (c+_{00}, c-_{NN}) are 0^gamma (constants stay integrated exactly there).
  * Errors: LBM_EINVAL for alpha outside (1,2], p outside [0,1], g <= 0, D not SPD
@@ -243,7 +245,8 @@ typedef struct {
  * floats each.  The forward states are checkpointed every ckpt_every steps
  * and recomputed per segment; the GEMMs of the reverse sweep run in FP32
  * whatever the handle's precision.  Device memory held by the handle after
- * the first call: ceil(n / ckpt_every) checkpoints of the populations, and two
+ * the first call: ceil(n / ckpt_every) checkpoints of the populations (and of C
+ * where it is carried beside them and fits), and two
  * segment buffers of ckpt_every steps (populations, C and the fractional
  * terms) when both fit (one otherwise: the recompute then no longer overlaps
  * the reverse sweep on the handle's internal second stream), and the reverse

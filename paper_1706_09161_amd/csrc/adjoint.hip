@@ -427,7 +427,7 @@ struct AdjointState {
     void* seg_mem[2] = {nullptr, nullptr};  // one allocation per segment buffer (the first also holds the checkpoints)
     void* fields = nullptr;                 // one allocation: fbar .. acc below
     float* ckpt = nullptr;   // populations at the start of every segment
-    float* ckptC = nullptr;  // and C there, where the collision reads it (cc.moments)
+    float* ckptC = nullptr;  // and C there, where the collision reads it (cc.moments) and it fits
     // recomputed segments, double-buffered (nbuf = 2) when both fit, so that
     // the next segment's recompute runs on a side stream during this
     // segment's reverse sweep
@@ -585,37 +585,6 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
     A->K = K;
     A->nseg = nseg;
     const size_t field = sizeof(float) * nodes, fq = field * Q;
-    for (int b = 0; b < 2; ++b) {
-        Slab slab;
-        const size_t of = slab.take(fq * (K + 1)), op = slab.take(field * d * K), oC = slab.take(field * K);
-        size_t ock = 0, ockC = 0;
-        if (b == 0) {
-            ock = slab.take(fq * nseg);
-            if (h->cc.moments) ockC = slab.take(field * nseg);
-        }
-        if (hipMalloc(&A->seg_mem[b], slab.bytes) != hipSuccess) {
-            // a second buffer is an optimisation: run single-buffered without it
-            (void)hipGetLastError();
-            A->seg_mem[b] = nullptr;
-            if (b == 0) return false;
-            break;
-        }
-        unsigned char* base = reinterpret_cast<unsigned char*>(A->seg_mem[b]);
-        A->seg_f[b] = reinterpret_cast<float*>(base + of);
-        A->seg_phi[b] = reinterpret_cast<float*>(base + op);
-        A->seg_C[b] = reinterpret_cast<float*>(base + oC);
-        if (b == 0) {
-            A->ckpt = reinterpret_cast<float*>(base + ock);
-            if (h->cc.moments) A->ckptC = reinterpret_cast<float*>(base + ockC);
-        }
-        A->nbuf = b + 1;
-    }
-    if (!A->side) {
-        if (hipStreamCreateWithFlags(&A->side, hipStreamNonBlocking) != hipSuccess) return false;
-        hipEvent_t* evs[] = {&A->ev_fwd, &A->ev_rec[0], &A->ev_rec[1], &A->ev_rev[0], &A->ev_rev[1]};
-        for (hipEvent_t* e : evs)
-            if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
-    }
     if (!A->fields) {
         const int64_t nb = (nodes + kBlock - 1) / kBlock;
         float** const f32[] = {&A->fbar,    &A->fdir,  &A->fdir2, &A->phibar, &A->phibar2, &A->tu,
@@ -636,6 +605,43 @@ bool alloc_state(lbm_fade* h, AdjointState* A, int64_t n, int K)
         slab = Slab();
         for (int k = 0; k < 11; ++k) *f32[k] = reinterpret_cast<float*>(base + slab.take(f32_bytes[k]));
         for (int k = 0; k < 3; ++k) *f64[k] = reinterpret_cast<double*>(base + slab.take(f64_bytes[k]));
+    }
+    // The checkpoints' C is left out where it does not fit (a segment then starts
+    // from the sum of its populations).
+    for (int b = 0; b < 2; ++b) {
+        Slab slab;
+        const size_t of = slab.take(fq * (K + 1)), op = slab.take(field * d * K), oC = slab.take(field * K);
+        const size_t ock = b == 0 ? slab.take(fq * nseg) : 0;
+        const size_t least = slab.bytes;
+        const size_t ockC = b == 0 && h->cc.moments ? slab.take(field * nseg) : 0;
+        bool ok = hipMalloc(&A->seg_mem[b], slab.bytes) == hipSuccess, withC = ockC != 0;
+        if (!ok && withC) {
+            (void)hipGetLastError();
+            withC = false;
+            ok = hipMalloc(&A->seg_mem[b], least) == hipSuccess;
+        }
+        if (!ok) {
+            // a second buffer is an optimisation: run single-buffered without it
+            (void)hipGetLastError();
+            A->seg_mem[b] = nullptr;
+            if (b == 0) return false;
+            break;
+        }
+        unsigned char* base = reinterpret_cast<unsigned char*>(A->seg_mem[b]);
+        A->seg_f[b] = reinterpret_cast<float*>(base + of);
+        A->seg_phi[b] = reinterpret_cast<float*>(base + op);
+        A->seg_C[b] = reinterpret_cast<float*>(base + oC);
+        if (b == 0) {
+            A->ckpt = reinterpret_cast<float*>(base + ock);
+            if (withC) A->ckptC = reinterpret_cast<float*>(base + ockC);
+        }
+        A->nbuf = b + 1;
+    }
+    if (!A->side) {
+        if (hipStreamCreateWithFlags(&A->side, hipStreamNonBlocking) != hipSuccess) return false;
+        hipEvent_t* evs[] = {&A->ev_fwd, &A->ev_rec[0], &A->ev_rec[1], &A->ev_rev[0], &A->ev_rev[1]};
+        for (hipEvent_t* e : evs)
+            if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
     }
     return true;
 }
@@ -724,6 +730,7 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
         ADJ_TRY(hipMemcpyAsync(gCdev, gC, sizeof(float) * nodes, hipMemcpyHostToDevice, s));
         gC = gCdev;
     }
+    const bool keep_C = h->cc.moments && A->ckptC;
     // Segment sg recomputed into buffer b from its checkpoint: populations, C
     // and Phi of each of its steps.
     auto seg_len = [&](int64_t sg) { return (int)((sg * K + K <= n ? sg * K + K : n) - sg * K); };
@@ -732,7 +739,7 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     };
     auto recompute = [&](int64_t sg, int b, hipStream_t st) -> int {
         const int len = seg_len(sg);
-        if (h->cc.moments)
+        if (keep_C)
             ADJ_TRY(hipMemcpyAsync(A->seg_C[b], A->ckptC + sg * nodes, sizeof(float) * nodes,
                                    hipMemcpyDeviceToDevice, st));
         else
@@ -766,7 +773,7 @@ int adjoint_run(lbm_fade* h, int64_t n, int ckpt_every, const float* gC, int on_
     for (int64_t t = 0; t < n; ++t) {
         if (t % K == 0) {
             ADJ_TRY(hipMemcpyAsync(A->ckpt + (t / K) * Q * nodes, h->f[h->cur], fq, hipMemcpyDeviceToDevice, s));
-            if (h->cc.moments)
+            if (keep_C)
                 ADJ_TRY(hipMemcpyAsync(A->ckptC + (t / K) * nodes, h->C[h->cur], sizeof(float) * nodes,
                                        hipMemcpyDeviceToDevice, s));
         }

@@ -799,7 +799,6 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
         for (int b = 0; b < d; ++b) cc.H[a * d + b] = (float)(0.5 * ((a == b ? 1.0 : 0.0) - h->lam_inv[a * d + b]));
     h->free_times_one = params->collision == LBM_MRT;
     for (int k = 0; k < Q - d - 1; ++k) h->free_times_one = h->free_times_one && params->tau_free[k] == 1.0;
-    cc.moments = h->free_times_one;
     cc.dt = (float)grid->dt;
 
     // operator data and state, one allocation
@@ -810,10 +809,25 @@ int lbm_fade_create(const lbm_grid* grid, int32_t lattice, const lbm_params* par
     lbm::Slab slab;
     slab.take(bytes);
     const size_t of0 = slab.take(field * Q), of1 = slab.take(field * Q);
-    const size_t oC = slab.take(field), oC1 = h->free_times_one ? slab.take(field) : oC;
-    const size_t oPhi = slab.take(field * d), oflag = slab.take(sizeof(int) * 4);
-    hipError_t e = hipMalloc(&h->mem, slab.bytes);
+    const size_t oC = slab.take(field), oPhi = slab.take(field * d), oflag = slab.take(sizeof(int) * 4);
+    size_t oC1 = oC;
+    hipError_t e = hipErrorOutOfMemory;
+    if (h->free_times_one) {
+        lbm::Slab more = slab;
+        oC1 = more.take(field);
+        e = hipMalloc(&h->mem, more.bytes);
+        if (e != hipSuccess) {
+            // no room for the second C: the collision operator does without
+            (void)hipGetLastError();
+            h->mem = nullptr;
+            h->free_times_one = false;
+            oC1 = oC;
+        }
+    }
+    cc.moments = h->free_times_one;
+    if (!h->mem) e = hipMalloc(&h->mem, slab.bytes);
     if (e != hipSuccess) {
+        h->mem = nullptr;
         cleanup();
         return fail(LBM_ENOMEM, "hipMalloc of the operator data and the solver state failed");
     }

@@ -32,7 +32,7 @@ struct lbm_fade {
     bool var_D = false;           // dB set by lbm_fade_set_diffusion (else zero)
     bool var_wall = false;        // Cw set by lbm_fade_set_wall (else c_wall)
     bool register_kernels = false;  // dense axes on the register kernels (lbm_fade_set_register_kernels)
-    bool free_times_one = false;    // MRT with every free relaxation time 1: collision in moments
+    bool free_times_one = false;    // MRT with every free relaxation time 1 (and memory for C[1]): collision in moments
     void* mem = nullptr;  // one allocation: the operator data of all axes, f, C, Phi and flag
     int* flag = nullptr;
     lbm::AxisData ops[3];

@@ -1,0 +1,87 @@
+"""What fits on the device without the second concentration field of the
+collision in moments still runs: a handle falls back to the collision operator,
+an adjoint to checkpoints without C.  The rest of the device's memory is held
+by one tensor meanwhile."""
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _hold_until_too_little(size, step):
+    """Tensors that leave less than `size` bytes of the device free, and at least
+    `size` less a few `step`: what the runtime reports as free is not what it
+    still gives, so this asks for it."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    if free < 2 * size:
+        pytest.skip("too little device memory is free")
+    held = [torch.empty(free - 2 * size, dtype=torch.uint8, device="cuda")]
+    try:
+        while True:
+            probe = torch.empty(size, dtype=torch.uint8, device="cuda")
+            del probe
+            torch.cuda.empty_cache()
+            held.append(torch.empty(step, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        torch.cuda.empty_cache()
+    return held
+
+
+def test_handle_without_room_for_a_second_C():
+    from paper_1706_09161_amd import LbmFade
+
+    n = [4352, 4224]  # beyond the boxes' 4096 nodes
+    field = 4 * n[0] * n[1]
+    cfg = synth.small(2, n, seed=95)
+    C0 = synth.initial_C(cfg).astype(np.float32)
+    held = _hold_until_too_little(14 * field, field // 2)  # 2 Q + 1 + d = 13 fields and the second C
+    try:
+        with LbmFade.from_config(cfg, precision="fp32") as s:
+            s.set_C(C0)
+            s.step(3)
+            got = s.get_C(device=False)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    with LbmFade.from_config(cfg, precision="fp32") as s:
+        s.set_register_kernels(True)
+        s.set_C(C0)
+        s.step(3)
+        assert np.array_equal(got, s.get_C(device=False))
+
+
+def test_adjoint_without_room_for_the_checkpoints_C():
+    from paper_1706_09161_amd import LbmFade
+
+    n, steps = [1024, 640], 40
+    field = 4 * n[0] * n[1]
+    cfg = synth.small(2, n, seed=96)
+    C0 = synth.initial_C(cfg).astype(np.float32)
+    gC = np.random.default_rng(97).uniform(-1.0, 1.0, C0.shape).astype(np.float32)
+
+    def run(left):
+        with LbmFade.from_config(cfg, precision="fp32") as s:
+            s.set_C(torch.from_numpy(C0).cuda())
+            g = torch.from_numpy(gC).cuda()
+            held = _hold_until_too_little(left, 30 * field) if left else None
+            try:
+                grads, _, _ = s.adjoint(steps, 1, g, want_fields=False)
+            finally:
+                del held
+                torch.cuda.empty_cache()
+            return grads, s.get_C(device=False)
+
+    # work fields 3 Q + 4 d + 4 = 27, checkpoints 5 a step, a segment of one
+    # step 2 Q + d + 1 = 13; C of the checkpoints one a step
+    got = run((27 + 6 * steps + 13) * field)
+    ref = run(0)
+    for key in ("D", "u", "p"):
+        assert np.allclose(got[0][key], ref[0][key], rtol=1e-4, atol=1e-4 * np.abs(ref[0][key]).max()), key
+    assert np.linalg.norm(got[1] - ref[1]) <= 1e-5 * np.linalg.norm(ref[1])
