@@ -116,6 +116,32 @@ __device__ __forceinline__ float flux_delta(const float (&dev)[Q], const float* 
     return s;
 }
 
+// What a collide-stream kernel needs of CollideConsts: one matrix, the operator
+// R or the H of the collision in moments, not both, and the two different
+// weights once.  The whole of it, 352 bytes in place of 160 (2D, operator) or 80
+// (moments), costs a step 0.1 to 0.3 us (us, all of it / this: 64^2 operator
+// 9.23 / 8.91, moments 8.50 / 8.36; 64^3 operator 13.5 / 13.2; 112^3 operator
+// 46.4 / 45.5).
+template <int Q, bool MOMENTS>
+struct NodeConsts {
+    static constexpr int d = (Q - 1) / 2;
+    const float *dB, *Cw;
+    int n[3];
+    float w0, wi;      // lattice weights (rest, moving)
+    float wS0, wSi;    // times dt (source)
+    float dt, c_wall;
+    float adv[d];
+    float M[MOMENTS ? d * d : Q * Q];
+
+    explicit NodeConsts(const CollideConsts& cc)
+        : dB(cc.dB), Cw(cc.Cw), w0(cc.w[0]), wi(cc.w[1]), wS0(cc.wSdt[0]), wSi(cc.wSdt[1]), dt(cc.dt), c_wall(cc.c_wall)
+    {
+        for (int a = 0; a < 3; ++a) n[a] = cc.n[a];
+        for (int a = 0; a < d; ++a) adv[a] = cc.adv[a];
+        for (int k = 0; k < (MOMENTS ? d * d : Q * Q); ++k) M[k] = MOMENTS ? cc.H[k] : cc.R[k];
+    }
+};
+
 // The equilibrium carries the node's mass: sum_i f^eq_i = C = sum_i f_i
 // (equation (Feq)), so the deviations f - f^eq have zero sum and the collision
 // conserves mass.  In FP32 the rounded f^eq_i leave a sum of a few ulp of C,
@@ -135,7 +161,7 @@ __device__ __forceinline__ void remove_mass_defect(float (&dev)[Q])
 }
 
 template <int Q, bool VAR>
-__device__ inline void collide_node(const CollideConsts& cc, const float (&f)[Q], const float (&phi)[(Q - 1) / 2],
+__device__ inline void collide_node(const NodeConsts<Q, false>& cc, const float (&f)[Q], const float (&phi)[(Q - 1) / 2],
                                     float S, const float* db, float (&fs)[Q])
 {
     // Products are fused only where fmaf says so (and fmaf is used wherever a
@@ -152,10 +178,10 @@ __device__ inline void collide_node(const CollideConsts& cc, const float (&f)[Q]
     float sphi = 0.f;
 #pragma unroll
     for (int mu = 0; mu < d; ++mu) sphi += phi[mu];
-    feq[0] = fmaf(-cc.w[0], sphi, C);
+    feq[0] = fmaf(-cc.w0, sphi, C);
 #pragma unroll
     for (int mu = 0; mu < d; ++mu) {
-        const float a = cc.w[2 * mu + 1] * phi[mu];
+        const float a = cc.wi * phi[mu];
         feq[2 * mu + 1] = fmaf(cc.adv[mu], C, a);
         feq[2 * mu + 2] = fmaf(-cc.adv[mu], C, a);
     }
@@ -167,9 +193,9 @@ __device__ inline void collide_node(const CollideConsts& cc, const float (&f)[Q]
     for (int i = 0; i < Q; ++i) {
         float r = 0.f;
 #pragma unroll
-        for (int j = 0; j < Q; ++j) r = fmaf(cc.R[i * Q + j], dev[j], r);
+        for (int j = 0; j < Q; ++j) r = fmaf(cc.M[i * Q + j], dev[j], r);
         fs[i] = f[i] - r;
-        fs[i] = fmaf(cc.wSdt[i], S, fs[i]);
+        fs[i] = fmaf(i == 0 ? cc.wS0 : cc.wSi, S, fs[i]);
     }
     if (VAR) {
 #pragma unroll
@@ -184,7 +210,7 @@ __device__ inline void collide_node(const CollideConsts& cc, const float (&f)[Q]
 // Post-collision populations 1 and 2 (the two that cross x) of one node (a
 // halo node at a strip edge).  With VAR, db holds row 0 of the node's dB.
 template <int Q, bool VAR>
-__device__ inline void collide_x_pair(const CollideConsts& cc, const float (&f)[Q], const float (&phi)[(Q - 1) / 2],
+__device__ inline void collide_x_pair(const NodeConsts<Q, false>& cc, const float (&f)[Q], const float (&phi)[(Q - 1) / 2],
                                       float S, const float* db, float& f1, float& f2)
 {
     // the same operations as collide_node's populations 1 and 2, fused alike
@@ -197,10 +223,10 @@ __device__ inline void collide_x_pair(const CollideConsts& cc, const float (&f)[
     float sphi = 0.f;
 #pragma unroll
     for (int mu = 0; mu < d; ++mu) sphi += phi[mu];
-    feq[0] = fmaf(-cc.w[0], sphi, C);
+    feq[0] = fmaf(-cc.w0, sphi, C);
 #pragma unroll
     for (int mu = 0; mu < d; ++mu) {
-        const float x = cc.w[2 * mu + 1] * phi[mu];
+        const float x = cc.wi * phi[mu];
         feq[2 * mu + 1] = fmaf(cc.adv[mu], C, x);
         feq[2 * mu + 2] = fmaf(-cc.adv[mu], C, x);
     }
@@ -211,11 +237,11 @@ __device__ inline void collide_x_pair(const CollideConsts& cc, const float (&f)[
     float ra = 0.f, rb = 0.f;
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-        ra = fmaf(cc.R[1 * Q + j], dev[j], ra);
-        rb = fmaf(cc.R[2 * Q + j], dev[j], rb);
+        ra = fmaf(cc.M[1 * Q + j], dev[j], ra);
+        rb = fmaf(cc.M[2 * Q + j], dev[j], rb);
     }
-    f1 = fmaf(cc.wSdt[1], S, f[1] - ra);
-    f2 = fmaf(cc.wSdt[2], S, f[2] - rb);
+    f1 = fmaf(cc.wSi, S, f[1] - ra);
+    f2 = fmaf(cc.wSi, S, f[2] - rb);
     if (VAR) {
         // row 0 of dB: db[b] = dB_0b
         float s = 0.f;
@@ -279,7 +305,7 @@ __device__ __forceinline__ void moments_of(const float (&v)[fields_in<Q, FORM>],
 // g_a of axis a (see above).  With VAR the node's H is the constant one less
 // half the node's dB (dB = 0 gives the constant path's bits).
 template <int Q, bool VAR>
-__device__ __forceinline__ float flux_part(const CollideConsts& cc, float C, const float (&j)[(Q - 1) / 2],
+__device__ __forceinline__ float flux_part(const NodeConsts<Q, true>& cc, float C, const float (&j)[(Q - 1) / 2],
                                            const float* db, int a)
 {
 #pragma clang fp contract(off)
@@ -287,7 +313,7 @@ __device__ __forceinline__ float flux_part(const CollideConsts& cc, float C, con
     float h = 0.f;
 #pragma unroll
     for (int b = 0; b < d; ++b) {
-        float H = cc.H[a * d + b];
+        float H = cc.M[a * d + b];
         if (VAR) H = fmaf(-0.5f, db[a <= b ? sym_index(d, a, b) : sym_index(d, b, a)], H);
         h = fmaf(H, fmaf(-2.f * cc.adv[b], C, j[b]), h);
     }
@@ -297,7 +323,7 @@ __device__ __forceinline__ float flux_part(const CollideConsts& cc, float C, con
 // Collision of a node: its post-collision populations; in the moment forms
 // fs[0] is C + S dt instead of f*_0 (see stream).
 template <int Q, int FORM, bool VAR>
-__device__ __forceinline__ void collide(const CollideConsts& cc, const float (&v)[fields_in<Q, FORM>],
+__device__ __forceinline__ void collide(const NodeConsts<Q, FORM != kPopulations>& cc, const float (&v)[fields_in<Q, FORM>],
                                         const float (&phi)[(Q - 1) / 2], float S, const float* db, float (&fs)[Q])
 {
 #pragma clang fp contract(off)
@@ -309,10 +335,10 @@ __device__ __forceinline__ void collide(const CollideConsts& cc, const float (&v
         moments_of<Q, FORM>(v, C, j);
 #pragma unroll
         for (int a = 0; a < d; ++a) {
-            const float e = cc.w[2 * a + 1] * phi[a];
+            const float e = cc.wi * phi[a];
             const float g = flux_part<Q, VAR>(cc, C, j, db, a);
-            fs[2 * a + 1] = fmaf(cc.wSdt[2 * a + 1], S, e + g);
-            fs[2 * a + 2] = fmaf(cc.wSdt[2 * a + 2], S, e - g);
+            fs[2 * a + 1] = fmaf(cc.wSi, S, e + g);
+            fs[2 * a + 2] = fmaf(cc.wSi, S, e - g);
         }
         fs[0] = fmaf(cc.dt, S, C);
     }
@@ -320,7 +346,7 @@ __device__ __forceinline__ void collide(const CollideConsts& cc, const float (&v
 
 // Populations 1 and 2 only (a halo node at a strip edge)
 template <int Q, int FORM, bool VAR>
-__device__ __forceinline__ void collide_pair(const CollideConsts& cc, const float (&v)[fields_in<Q, FORM>],
+__device__ __forceinline__ void collide_pair(const NodeConsts<Q, FORM != kPopulations>& cc, const float (&v)[fields_in<Q, FORM>],
                                              const float (&phi)[(Q - 1) / 2], float S, const float* db, float& f1,
                                              float& f2)
 {
@@ -331,10 +357,10 @@ __device__ __forceinline__ void collide_pair(const CollideConsts& cc, const floa
     } else {
         float C, j[d];
         moments_of<Q, FORM>(v, C, j);
-        const float e = cc.w[1] * phi[0];
+        const float e = cc.wi * phi[0];
         const float g = flux_part<Q, VAR>(cc, C, j, db, 0);
-        f1 = fmaf(cc.wSdt[1], S, e + g);
-        f2 = fmaf(cc.wSdt[2], S, e - g);
+        f1 = fmaf(cc.wSi, S, e + g);
+        f2 = fmaf(cc.wSi, S, e - g);
     }
 }
 
@@ -399,7 +425,7 @@ __device__ __forceinline__ void finish_node(const float (&fs)[Q], float (&f)[Q],
 // 2D D2Q5 fused kernel.  Rows move through a ring of D slots: while row y + 1
 // is collided, the loads of rows y + 2 .. y + D are in flight.
 template <int FORM, bool HAS_S, bool VAR, bool NT, typename OFF>
-__global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const float* __restrict__ fin,
+__global__ __launch_bounds__(256) void collide_stream_2d(NodeConsts<5, FORM != kPopulations> cc, const float* __restrict__ fin,
                                                          const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                          const float* __restrict__ S, float* __restrict__ Cout,
                                                          int rows_per_wave, int strips, int total_waves)
@@ -525,7 +551,7 @@ __global__ __launch_bounds__(256) void collide_stream_2d(CollideConsts cc, const
 // is collided).  f*_3 / f*_4 cross rows through LDS, double-buffered by plane
 // parity so one barrier per plane suffices.
 template <int FORM, int NY, bool HAS_S, bool VAR, bool NT, typename OFF>
-__global__ __launch_bounds__(64 * NY) void collide_stream_3d(CollideConsts cc, const float* __restrict__ fin,
+__global__ __launch_bounds__(64 * NY) void collide_stream_3d(NodeConsts<7, FORM != kPopulations> cc, const float* __restrict__ fin,
                                                              const float* __restrict__ Cin, float* __restrict__ fout, const float* __restrict__ Phi,
                                                              const float* __restrict__ S, float* __restrict__ Cout,
                                                              int planes_per_block, int strips_x, int strips_y)
@@ -827,17 +853,18 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, con
         const int chunks = (ny + rows - 1) / rows;
         const int waves = strips * chunks;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, rows, strips,
+        auto go = [&](auto kern, const auto& nc) {
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, nc, f_in, C_in, f_out, Phi, S, C_out, rows, strips,
                                waves);
         };
         with_form([&](auto form, auto hs, auto vr, auto ntc) {
             constexpr bool HS = decltype(hs)::value, VR = decltype(vr)::value, NT = decltype(ntc)::value;
             constexpr int F = decltype(form)::value;
+            const NodeConsts<5, F != kPopulations> nc(cc);
             if constexpr (F <= kMomentCollision) {
-                if (!small) return go(collide_stream_2d<F, HS, VR, NT, uint64_t>);
+                if (!small) return go(collide_stream_2d<F, HS, VR, NT, uint64_t>, nc);
             }
-            go(collide_stream_2d<F, HS, VR, NT, uint32_t>);
+            go(collide_stream_2d<F, HS, VR, NT, uint32_t>, nc);
         });
         return hipGetLastError();
     }
@@ -889,7 +916,8 @@ hipError_t launch_collide_stream(const CollideConsts& cc, const float* f_in, con
         if constexpr (F <= kMomentCollision) {
             if (!small) kern = collide_stream_3d<F, NY, HS, VR, NT, uint64_t>;
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, cc, f_in, C_in, f_out, Phi, S, C_out, planes,
+        const NodeConsts<7, F != kPopulations> nc(cc);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NY), 0, s, nc, f_in, C_in, f_out, Phi, S, C_out, planes,
                            sx, sy);
         return hipSuccess;
     };
