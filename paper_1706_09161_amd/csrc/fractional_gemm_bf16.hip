@@ -818,7 +818,7 @@ __global__ __launch_bounds__(kThreads, NBJ <= 4 ? 2 : 1) void fractional_bf16x3_
     while (axis + 1 < L.naxes && bid >= L.first[axis + 1]) ++axis;
     const int local = bid - L.first[axis];
     const int total = L.first[axis + 1] - L.first[axis];
-    if (axis == 0 && L.lay[0].contiguous)
+    if (axis == 0)
         bf16x3_ring_tile<true, NBJ, WL, KSPLIT, P, VEC_X, KFULL>(L.op[0], L.lay[0], L.C[0], L.Phi[0], L.tiles_m[0],
                                                           L.tiles_n[0], local, total, smem_r);
     else
@@ -868,13 +868,9 @@ hipError_t run_ring(FracLaunch& L, hipStream_t s)
         return hipGetLastError();
     };
     bool kfull = true;  // every axis a multiple of 16: no step passes the end of an axis
-    bool vec = true;    // the contiguous axis (if in this launch) a multiple of 8
-    for (int a = 0; a < L.naxes; ++a) {
-        kfull = kfull && (L.op[a].n % 16) == 0;
-        vec = vec && (!L.lay[a].contiguous || (L.op[a].n % 8) == 0);
-    }
+    for (int a = 0; a < L.naxes; ++a) kfull = kfull && (L.op[a].n % 16) == 0;
     if (kfull) return go(fractional_bf16x3_ring<NBJ, WL, KSPLIT, P, true, true>);
-    if (vec) return go(fractional_bf16x3_ring<NBJ, WL, KSPLIT, P, true, false>);
+    if (L.op[0].n % 8 == 0) return go(fractional_bf16x3_ring<NBJ, WL, KSPLIT, P, true, false>);
     return go(fractional_bf16x3_ring<NBJ, WL, KSPLIT, P, false, false>);
 }
 
