@@ -62,7 +62,9 @@ enum { LBM_BGK = 0, LBM_MRT = 1 };
 
 /* Arithmetic of the fractional-term GEMM.  Weights are always generated in FP64.
  *   LBM_FP32   FP32 operands and FP32 accumulation, as exact three-term BF16
- *              splits on BF16 MFMA, or on FP32 MFMA where that is faster;
+ *              splits on BF16 MFMA, or on FP32 MFMA where that is faster; the
+ *              splits keep values below about 1e-33 to 5e-41 absolute only
+ *              (lbm_fade_set_register_kernels and LBM_FP32_SIMT keep all 24 bits);
  *   LBM_BF16X3 3-term split BF16: W = W_hi + W_lo, C = C_hi + C_lo (round to
  *              nearest even), W_hi C_hi + W_hi C_lo + W_lo C_hi on BF16 MFMA with
  *              FP32 accumulation (the lo*lo term is dropped);

@@ -35,8 +35,7 @@
 //
 // Measured (us per launch, both axes, graph replay; before: the dense FP32
 // kernels), one-sided p = (1, 0) / two-sided p = (0.3, 0.8): 4096^2 1113 / 2106
-// -> 118 / 158, 2048^2 183 / 272 -> 39 / 48, 1024^2 39 / 41 -> 18 / 21,
-// 801 x 650 35 / 37 -> 16 / 19.
+// -> 118 / 158, 2048^2 183 / 272 -> 39 / 48, 1024^2 39 / 41 -> 18 / 21.
 // At 4096^2 the moments read C at 7 TB/s; of the band's time half is matrix
 // work, the rest the split of C, its loads and the stores.  Below about 1500
 // nodes one wavefront per SIMD runs load, moments, local coefficients and band
@@ -44,7 +43,9 @@
 // 3.4k, moments 14k, local 4k, band 10k, stores 3k).  Errors against 64 bits
 // (relative L2, pulses, dense FP32 in brackets): 1024^2 5.7e-8 / 6.2e-8 (6.0e-8
 // / 8.0e-8), 4096^2 5.7e-8 / 5.9e-8 (5.2e-8 / 7.8e-8); random C 6.1e-8 / 6.4e-8
-// (8.0e-8 / 9.5e-8) and 6.2e-8 / 7.0e-8 (1.0e-7 / 2.6e-7).
+// (8.0e-8 / 9.5e-8) and 6.2e-8 / 7.0e-8 (1.0e-7 / 2.6e-7).  Adding the three
+// accumulators with the first sum's rounding carried along takes about 5e-9 off
+// each, and 2 to 4 % more time (4096^2 one-sided 115.8 -> 120.7 us).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -496,10 +497,13 @@ bool far_reaches(const AxisLayout& lay, int n)
 
 bool far_used(int n)
 {
-    // Upper end: the moments of 32 lines (16 BF16 triples per 128 nodes and
-    // line) fill the LDS.  Lower end: there the band and the two box steps cost
-    // as much as the dense sum (FP32, far / dense, us: 640^2 16.4 / 12.9, 768^2
-    // 17.9 / 18.5, 896 x 900 18.4 / 24.2, 1024^2 19.3 / 26.0).
+    // Upper end: the longest axis this was measured on, and the one up to which
+    // the third plane of the weights is made (kThirdPlaneMax); the moments of 32
+    // lines (16 BF16 triples per 128 nodes and line) fill the LDS at 4288 nodes.
+    // Longer axes are summed densely, as they were: 4097^2 costs 10 times 4096^2.
+    // Lower end: there the band and the two box steps cost as much as the dense
+    // sum (FP32, far / dense, us: 640^2 16.4 / 12.9, 768^2 17.9 / 18.5, 896 x 900
+    // 18.4 / 24.2, 1024^2 19.3 / 26.0).
     return n > 768 && n <= 4096;
 }
 

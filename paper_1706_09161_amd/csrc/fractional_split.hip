@@ -25,7 +25,7 @@
 // kernels before), one-sided / two-sided: FP32 256^3 110 / 141 (221 / 221),
 // 200 x 150 x 170 49 / 55 (140 / 140), 128^3 18 / 19 (27 / 27), 90 x 75 x 61
 // 8.1 / 8.6 (14.9 / 14.9), 64^3 5.8 / 5.9 (8.3 / 7.6), 201 x 101 6.0 (8.9 /
-// 8.8), 333 x 500 9.2 / 9.5 (12.5 / 12.8), 64^2 4.9 (5.2); split BF16 256^3 79 /
+// 8.8), 333 x 500 9.2 / 9.5 (12.5 / 12.8), 64^2 4.6 (5.1); split BF16 256^3 79 /
 // 92 (119 / 126), 90 x 75 x 61 7.3 / 7.7 (15.9 / 15.7), 201 x 101 5.5 (11.9 /
 // 11.4), 64^2 4.7 (7.2).  Errors of the FP32 sums fall too (256^3 relative L2
 // 2.9e-7 -> 6.8e-8: three accumulators, 16 products a rounding).  At 256^3 the

@@ -1,9 +1,15 @@
 // split_fragments.h -- device pieces shared by the kernels that run FP32
-// contractions on the BF16 matrix cores (fractional_far.hip).  Not part of the public ABI.
+// contractions on the BF16 matrix cores (fractional_split.hip, fractional_far.hip).
+// Not part of the public ABI.
 //
 // An FP32 value is the exact sum of three BF16 values, x = h + m + l with
 // h = bf16(x), m = bf16(x - h), l = x - h - m (round to nearest even; the two
-// differences are exact and the last one fits 8 bits), so
+// differences are exact and the last one fits 8 bits) as long as l is no finer
+// than BF16's smallest subnormal, 2^-133: for |x| from 2^-110 (8e-34) up.  Below,
+// x is kept to 2^-134 absolute (a field scaled by 2^-114: relative L2 of the sum
+// 1.3e-7 instead of 4.6e-8, by 2^-120 8e-6; the FP32 register kernels keep
+// 4.6e-8).  Scaling C by 2^16 before the split keeps every bit down there, at two
+// more instructions a pair: 1 to 3 % of every launch, 7 % at 2048^2.  So
 //   K C = K_h C_h + (K_h C_m + K_m C_h) + (K_h C_l + K_m C_m + K_l C_h) + ...
 // where the three products left out are at most 2^-26 of the first.  Weights
 // are split from their FP64 values (27 bits).  The first product goes into

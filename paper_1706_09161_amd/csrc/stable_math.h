@@ -8,9 +8,13 @@
 // the exponential no more than a rounding.  The arguments V, a (V + B) and
 // V - a (V + B) lie in [-pi, pi]: sine and cosine need one fold and one
 // polynomial, no reduction by multiples of pi/2.  Methods: table-driven
-// logarithm (P. T. P. Tang, ACM TOMS 16, 1990), Taylor polynomials of sine and
-// exponential on [0, pi/2] and [-log 2 / 2, log 2 / 2] (truncation below 2^-58),
-// error-free sums and products (Dekker 1971, Knuth).
+// logarithm (P. T. P. Tang, ACM TOMS 16, 1990; its reduction, x 2^-k from 0.6875
+// indexed by 7 bits of the high word with c = 1 next to 1 and log 2 cut at a
+// multiple of 2^-42, makes the choices of the open log of Arm's optimized
+// routines, which glibc has too; the table, with c of 24 bits, and what follows
+// it are this file's), Taylor polynomials of sine and exponential on [0, pi/2]
+// and [-log 2 / 2, log 2 / 2] (truncation below 2^-58), error-free sums and
+// products (Dekker 1971, Knuth).
 //
 // Relative error of S against 128-bit arithmetic on the same rounded arguments,
 // 4e6 draws over a in (1, 2], beta in [-1, 1] and the ends of the uniforms, rms
