@@ -22,8 +22,9 @@ def _hold_until_too_little(size, step):
     free, _ = torch.cuda.mem_get_info()
     if free < 2 * size:
         pytest.skip("too little device memory is free")
-    held = [torch.empty(free - 2 * size, dtype=torch.uint8, device="cuda")]
+    held = []
     try:
+        held.append(torch.empty(free - 2 * size, dtype=torch.uint8, device="cuda"))
         while True:
             probe = torch.empty(size, dtype=torch.uint8, device="cuda")
             del probe
@@ -31,6 +32,8 @@ def _hold_until_too_little(size, step):
             held.append(torch.empty(step, dtype=torch.uint8, device="cuda"))
     except torch.cuda.OutOfMemoryError:
         torch.cuda.empty_cache()
+    if not held:
+        pytest.skip("the device's memory cannot be held")
     return held
 
 
